@@ -174,6 +174,11 @@ int stage_and_launch(int device, hipStream_t st, size_t n, int num_cus, Fill fil
         // extra messages looping in grid strides.
         const uint32_t groups = (m + 255) / 256;
         const int grid = static_cast<int>(std::min<uint32_t>(groups, static_cast<uint32_t>(16 * num_cus)));
+        // Up to two of the split kernel's workgroups (64 messages, three
+        // waves) per CU its shorter chain wins: 4 KiB messages, per call,
+        // 16,384 of them 111 against 193 us, 32,768 181 against 197, 49,152
+        // 239 against 201 (by then one lane per message fills the SIMDs).
+        const bool split = groups <= static_cast<uint32_t>(num_cus) / 2;
         const ShaRecord *recs = c->host_view[slot];
         if (first > 0 || hipStreamQuery(st) != hipSuccess) {
             // The upload may start at once: it waits for nothing on `st`
@@ -186,7 +191,7 @@ int stage_and_launch(int device, hipStream_t st, size_t n, int num_cus, Fill fil
                 hipStreamWaitEvent(st, c->uploaded[slot], 0) != hipSuccess)
                 return device_error();
         }
-        if ((rc = launch_sha256_batch(recs, m, grid, st)) != AES_OK)
+        if ((rc = launch_sha256_batch(recs, m, grid, split, st)) != AES_OK)
             return rc;
         if (hipEventRecord(c->done[slot], st) != hipSuccess)
             return device_error();

@@ -19,7 +19,9 @@ struct ShaRecord {
 
 constexpr uint32_t kMaxShaBatch = 1u << 17;   // records per launch (4 MiB table)
 
-int launch_sha256_batch(const ShaRecord *dev_recs, uint32_t n, int grid, hipStream_t st);
+// split: three waves per 64 messages (a grid of its own); else one lane per
+// message on `grid` workgroups of 256.
+int launch_sha256_batch(const ShaRecord *dev_recs, uint32_t n, int grid, bool split, hipStream_t st);
 
 // Validation of one message (AES_OK, AES_EINVAL, AES_ERANGE, AES_EOVERLAP).
 int check_sha(const void *in, uint64_t len, const void *digest);
