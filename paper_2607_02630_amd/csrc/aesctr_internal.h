@@ -169,7 +169,7 @@ struct alignas(64) BatchDesc {
     uint32_t k1[4];
     uint32_t tile0;
     uint32_t key;            // kKeyResident | slot, or an inline KeyRec index
-    uint16_t nr, aligned;    // aligned: in and out 16-byte aligned
+    uint32_t nr;
     uint32_t pad;
 };
 
@@ -211,7 +211,7 @@ struct SmallRec {
     uint32_t tile0;
     uint32_t key;            // kKeyResident | slot, or anything else = rk below
     uint32_t install;        // slot to write rk into, or kNoInstall
-    uint16_t nr, aligned;
+    uint32_t nr;
     uint32_t rk[60];
 };
 

@@ -206,7 +206,6 @@ int launch_small(hipStream_t st, const LaunchSpec &spec, uint32_t tile_blocks, i
         r.ctr0 = d.ctr0;
         r.x0 = d.x0;
         r.nr = d.nr;
-        r.aligned = d.aligned;
         memcpy(r.k1, d.k1, sizeof(r.k1));
         r.key = d.key;
         r.install = kNoInstall;
@@ -383,8 +382,7 @@ void make_batch_desc(const aes_ctr_desc_t &d, BatchDesc *o, KeyRec *k)
     o->len = d.len;
     o->ctr0 = d.ctr0;
     o->x0 = km.x0;
-    o->nr = static_cast<uint16_t>(km.nr);
-    o->aligned = ((o->in | o->out) & 15) == 0;
+    o->nr = static_cast<uint32_t>(km.nr);
     memcpy(o->k1, km.k1, sizeof(o->k1));
     memset(k, 0, sizeof(*k));
     memcpy(k->rk, km.rk, sizeof(km.rk));

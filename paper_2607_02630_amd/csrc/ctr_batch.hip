@@ -26,12 +26,6 @@ constexpr int kBatchLayout = kLayout4x32;
 constexpr int kSmallWG = 256;
 constexpr int kSmallLayout = kLayout2x32;
 
-// Request pointers arrive as integers; these types keep their accesses in the
-// global address space (global_load/store rather than flat).
-typedef __attribute__((address_space(1))) const u32x4 g_cu32x4;
-typedef __attribute__((address_space(1))) u32x4 g_u32x4;
-typedef __attribute__((address_space(1))) const uint8_t g_cu8;
-typedef __attribute__((address_space(1))) uint8_t g_u8;
 // Round keys are read through the constant address space, so they load with
 // scalar instructions even though workgroup 0 of the same launch writes
 // other slots of the resident table (installs): no launch reads a slot that
@@ -42,11 +36,12 @@ typedef __attribute__((address_space(4))) const uint32_t c_u32;
 // lane (the round-1/2 sharing needs the whole wave), and lane i of each step
 // holds block s0 + 64*b + i.  FULL: rounds 1-2 of every block in full
 // instead of from the wave's group constants.
-template <int NR, int LAYOUT, int BPL, bool ALIGNED, bool FULL>
+template <int NR, int LAYOUT, int BPL, bool FULL>
 __device__ __forceinline__ void run_tile(const TTable<LAYOUT> &tt, const CtrArgs &a, uint64_t b0,
                                          uint64_t b1, uint32_t lane)
 {
     const uint64_t nfull = a.len >> 4;
+    const uint32_t tail = static_cast<uint32_t>(a.len & 15);
     // rotr(rk, 8) of rounds 2..Nr-1 for the two-table fold (the four-table
     // layout reads none).
     uint32_t krot[60];
@@ -61,16 +56,11 @@ __device__ __forceinline__ void run_tile(const TTable<LAYOUT> &tt, const CtrArgs
         for (int b = 0; b < BPL; ++b) {
             const uint64_t idx = s0 + 64 * b + lane;
             ctr[b] = a.ctr0 + static_cast<uint32_t>(idx);
-            if (idx < b1 && idx < nfull) {
-                if constexpr (ALIGNED) {
-                    d[b] = __builtin_nontemporal_load((g_cu32x4 *)(uintptr_t)a.in + idx);
-                } else {
-                    g_cu8 *p = (g_cu8 *)(uintptr_t)a.in + 16 * idx;
-                    uint8_t tmp[16];
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) tmp[i] = p[i];
-                    __builtin_memcpy(&d[b], tmp, 16);
-                }
+            if (idx < b1) {
+                if (idx < nfull)
+                    d[b] = load_block(a.in, idx);
+                else
+                    d[b] = load_partial(a.in, nfull, tail);
             }
         }
         if constexpr (FULL) {
@@ -84,26 +74,11 @@ __device__ __forceinline__ void run_tile(const TTable<LAYOUT> &tt, const CtrArgs
             const uint64_t idx = s0 + 64 * b + lane;
             if (idx >= b1)
                 continue;
-            const u32x4 k = u32x4{ks[b][0], ks[b][1], ks[b][2], ks[b][3]};
-            if (idx < nfull) {
-                if constexpr (ALIGNED) {
-                    __builtin_nontemporal_store(d[b] ^ k, (g_u32x4 *)(uintptr_t)a.out + idx);
-                } else {
-                    const u32x4 v = d[b] ^ k;
-                    uint8_t tmp[16];
-                    __builtin_memcpy(tmp, &v, 16);
-                    g_u8 *p = (g_u8 *)(uintptr_t)a.out + 16 * idx;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) p[i] = tmp[i];
-                }
-            } else if (idx == nfull) {
-                // Final partial block: leading bytes of its keystream block.
-                const uint32_t tail = static_cast<uint32_t>(a.len & 15);
-                g_cu8 *src = (g_cu8 *)(uintptr_t)a.in + 16 * idx;
-                g_u8 *dst = (g_u8 *)(uintptr_t)a.out + 16 * idx;
-                for (uint32_t i = 0; i < tail; ++i)
-                    dst[i] = src[i] ^ static_cast<uint8_t>(k[i >> 2] >> (8 * (i & 3)));
-            }
+            const u32x4 v = d[b] ^ u32x4{ks[b][0], ks[b][1], ks[b][2], ks[b][3]};
+            if (idx < nfull)
+                store_block(a.out, idx, v);
+            else
+                store_partial(a.out, nfull, tail, v);
         }
     }
 }
@@ -134,17 +109,10 @@ __device__ __forceinline__ void request_tile(const TTable<LAYOUT> &tt, const Rec
     const uint64_t nblocks = (a.len + 15) >> 4;
     const uint64_t b0 = static_cast<uint64_t>(t - R.tile0) * tile_blocks;
     const uint64_t b1 = b0 + tile_blocks < nblocks ? b0 + tile_blocks : nblocks;
-    if (R.aligned) {
-        if (nr == 10)
-            run_tile<10, LAYOUT, BPL, true, FULL>(tt, a, b0, b1, lane);
-        else
-            run_tile<14, LAYOUT, BPL, true, FULL>(tt, a, b0, b1, lane);
-    } else {
-        if (nr == 10)
-            run_tile<10, LAYOUT, BPL, false, FULL>(tt, a, b0, b1, lane);
-        else
-            run_tile<14, LAYOUT, BPL, false, FULL>(tt, a, b0, b1, lane);
-    }
+    if (nr == 10)
+        run_tile<10, LAYOUT, BPL, FULL>(tt, a, b0, b1, lane);
+    else
+        run_tile<14, LAYOUT, BPL, FULL>(tt, a, b0, b1, lane);
 }
 
 // Writes the round keys of key record `src` (64 words) into slot `slot` of

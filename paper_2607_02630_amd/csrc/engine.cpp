@@ -488,7 +488,6 @@ extern "C" int aes_submit_at(aes_engine_t *e, const aes_ctr_desc_t *d, int64_t t
             return rc;
         r.rec.d.in = din;
         r.rec.d.out = dout;
-        r.rec.d.aligned = ((din | dout) & 15) == 0;
     }
     return e->core.submit(std::move(r), ticket, t_arrival_ns);
 }
