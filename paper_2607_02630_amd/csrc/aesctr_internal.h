@@ -142,7 +142,7 @@ int launch_ctr_vperm(const VpArgs &a, int nr, const Shape &sh, hipStream_t st);
 // Requests are cut into tiles of tile_blocks 16-byte blocks; tile0 is a
 // request's first tile (exclusive prefix sum), so tile t belongs to the last
 // request whose tile0 <= t.  next is the work counter the waves claim tiles
-// from; every upload carries it as 0.
+// from once each workgroup has done its own; every upload carries it as 0.
 constexpr int kMaxBatch = 4096;          // requests per launch (tile0 index in LDS)
 constexpr int kMaxBatchGrid = 1 << 20;   // workgroups per batch launch (keeps tile indices in 32 bits)
 // BatchDesc::key: kKeyResident | slot reads slot `slot` of the resident key
@@ -160,7 +160,8 @@ struct alignas(64) BatchHeader {
     uint32_t keys_off;       // byte offsets from the start of the table
     uint32_t install_off;
     uint64_t resident;       // device address of the resident key table, or 0
-    uint32_t pad[6];
+    uint32_t own_tiles;      // tiles each workgroup of the launch owns (see batch_own_tiles)
+    uint32_t pad[5];
 };
 
 struct alignas(64) BatchDesc {
@@ -261,11 +262,20 @@ void make_batch_record(const aes_ctr_desc_t &d, RequestRec *o);
 void make_batch_desc(const aes_ctr_desc_t &d, BatchDesc *o, KeyRec *k);
 int launch_spec(int device, hipStream_t st, const LaunchSpec &spec, int tile_bytes, int grid, int bpl,
                 bool use_graph, bool allow_small);
+// Tiles of a request: its blocks by position, the first at ctr0 mod 64 (see
+// run_tile), cut every tile_blocks.
+inline uint64_t request_tiles(uint64_t len, uint32_t ctr0, uint32_t tile_blocks)
+{
+    const uint64_t blocks = (len + 15) / 16;
+    return blocks ? ((ctr0 & 63u) + blocks + tile_blocks - 1) / tile_blocks : 0;
+}
+// Tiles that each of grid workgroups owns; the rest is claimed one by one.
+uint32_t batch_own_tiles(uint64_t tiles, int grid);
 // Completes a staged table of n requests at buf (descriptors, keys and
 // installs written, n_keys / n_install / resident set in the header):
 // assigns each request's first tile and fills the rest of the header.
 // Returns the table's bytes, or 0 if the tile count would overflow 31 bits.
-size_t finish_stage(uint8_t *buf, size_t n, uint32_t tile_blocks);
+size_t finish_stage(uint8_t *buf, size_t n, uint32_t tile_blocks, int grid);
 
 // Returns the staging context of stream st on device to the device's free
 // list (the stream is about to be destroyed; its work must have finished or

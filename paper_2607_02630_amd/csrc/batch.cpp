@@ -161,15 +161,25 @@ int build_graph(BatchCtx *c, int s, int grid, int bpl)
 // and header.n_install installs written.  Assigns first tiles and fills the
 // rest of the header.  Returns the bytes to upload, or 0 if the tile count
 // would overflow.
-size_t finish_stage(uint8_t *buf, size_t n, uint32_t tile_blocks)
+uint32_t batch_own_tiles(uint64_t tiles, int grid)
+{
+    // A claim from the header's counter is a device-wide atomic on one word:
+    // about 13 ns each, however many waves ask, and when every wave asks at
+    // its first tile the queue is 50 us long.  So a launch of few tiles makes
+    // none, and a large one leaves a twelfth to them, more than the CUs differ
+    // by at the end of equal shares (3-6%).
+    const uint64_t per_wg = (tiles + grid - 1) / grid;
+    return static_cast<uint32_t>(per_wg >= 64 ? per_wg - per_wg / 12 : per_wg);
+}
+
+size_t finish_stage(uint8_t *buf, size_t n, uint32_t tile_blocks, int grid)
 {
     BatchHeader *h = reinterpret_cast<BatchHeader *>(buf);
     BatchDesc *out = reinterpret_cast<BatchDesc *>(buf + sizeof(BatchHeader));
     uint64_t tiles = 0;
     for (size_t i = 0; i < n; ++i) {
         out[i].tile0 = static_cast<uint32_t>(tiles);
-        const uint64_t blocks = (out[i].len + 15) / 16;
-        tiles += (blocks + tile_blocks - 1) / tile_blocks;
+        tiles += request_tiles(out[i].len, out[i].ctr0, tile_blocks);
         if (tiles > 0x7fffffffu)
             return 0;
     }
@@ -177,6 +187,7 @@ size_t finish_stage(uint8_t *buf, size_t n, uint32_t tile_blocks)
     h->total_tiles = static_cast<uint32_t>(tiles);
     h->tile_blocks = tile_blocks;
     h->next = 0;
+    h->own_tiles = batch_own_tiles(tiles, grid);
     h->keys_off = static_cast<uint32_t>(batch_keys_off(n));
     h->install_off = static_cast<uint32_t>(batch_install_off(n, h->n_keys));
     memset(h->pad, 0, sizeof(h->pad));
@@ -216,7 +227,7 @@ int launch_small(hipStream_t st, const LaunchSpec &spec, uint32_t tile_blocks, i
                     r.install = spec.installs[j].slot;
         }
         r.tile0 = static_cast<uint32_t>(tiles);
-        tiles += ((d.len + 15) / 16 + tile_blocks - 1) / tile_blocks;
+        tiles += request_tiles(d.len, d.ctr0, tile_blocks);
         if (tiles > 0x7fffffffu)
             return AES_ERANGE;
     }
@@ -312,7 +323,7 @@ int launch_spec(int device, hipStream_t st, const LaunchSpec &spec, int tile_byt
     memcpy(buf + sizeof(BatchHeader), spec.descs, spec.n * sizeof(BatchDesc));
     memcpy(buf + batch_keys_off(spec.n), spec.keys, spec.n_keys * sizeof(KeyRec));
     memcpy(buf + batch_install_off(spec.n, spec.n_keys), spec.installs, spec.n_install * sizeof(InstallRec));
-    const size_t bytes = finish_stage(buf, spec.n, tile_blocks);
+    const size_t bytes = finish_stage(buf, spec.n, tile_blocks, grid);
     if (bytes == 0)
         return AES_ERANGE;
     return submit_slot(c, slot, bytes, st, grid, bpl, use_graph);
@@ -511,7 +522,7 @@ extern "C" int aes_ctr_crypt_batch_cfg(const aes_ctr_desc_t *desc, size_t n, con
                 out[i].key = static_cast<uint32_t>(i);
             }
         });
-        const size_t bytes = finish_stage(buf, m, tile_blocks);
+        const size_t bytes = finish_stage(buf, m, tile_blocks, sh.grid);
         if (bytes == 0)
             return AES_ERANGE;
         if ((rc = submit_slot(c, slot, bytes, st, sh.grid, sh.bpl, sh.use_graph != 0)) != AES_OK)

@@ -123,7 +123,7 @@ extern "C" int aes_ctr_crypt_batch_noalloc(const aes_ctr_desc_t *desc, size_t n,
             make_batch_desc(desc[first + i], &dpiece[i], &kpiece[i]);
             dpiece[i].key = static_cast<uint32_t>(first + i);
             dpiece[i].tile0 = static_cast<uint32_t>(tiles);
-            tiles += ((dpiece[i].len + 15) / 16 + tile_blocks - 1) / tile_blocks;
+            tiles += request_tiles(dpiece[i].len, dpiece[i].ctr0, tile_blocks);
             if (tiles > 0x7fffffffu)
                 return AES_ERANGE;
         }
@@ -134,8 +134,9 @@ extern "C" int aes_ctr_crypt_batch_noalloc(const aes_ctr_desc_t *desc, size_t n,
             return rc;
     }
     h.total_tiles = static_cast<uint32_t>(tiles);
+    const uint64_t grid = tiles < static_cast<uint64_t>(di.num_cus) ? (tiles ? tiles : 1) : di.num_cus;
+    h.own_tiles = batch_own_tiles(tiles, static_cast<int>(grid));
     if ((rc = copy_in(table, &h, sizeof(h), st)) != AES_OK)
         return rc;
-    const uint64_t grid = tiles < static_cast<uint64_t>(di.num_cus) ? (tiles ? tiles : 1) : di.num_cus;
     return launch_ctr_batch(table, static_cast<int>(grid), 1024, bpl, st);
 }

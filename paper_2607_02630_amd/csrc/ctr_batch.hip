@@ -2,14 +2,19 @@
 //
 // Each workgroup fills the bank-replicated T-tables into LDS once (the same
 // round code as the single-buffer kernel, ttable_device.h), copies the
-// requests' first-tile indices into LDS, then its waves claim tiles from a
-// device counter until the table is exhausted.  A tile is tile_blocks
+// requests' first-tile indices into LDS, then its waves take the workgroup's
+// own tiles from a counter in LDS and, in a large batch, the last twelfth from
+// a device counter.  A tile is tile_blocks
 // consecutive 16-byte blocks of one request; the wave finds the request by a
 // binary search over the tile indices in LDS and reads that request's key
 // material, pointers and counter parameters with scalar loads (they are the
 // same for the whole wave).  Requests of any size, key length (AES-128 and
 // AES-256 mixed) and alignment share the launch; dynamic claiming balances
 // the log-uniform size mix.
+//
+// Bound: 4.5 GB in 4096 requests takes 3.1 ms at 128 (AES-128) or 192 table
+// lookups per block, 27 of the 28.6 per clock and CU that the LDS gives, at the
+// 2.0-2.1 GHz the card holds under this load (2.4 without the payload traffic).
 #include <stddef.h>
 
 #include "ttable_device.h"
@@ -21,8 +26,7 @@ constexpr int kBatchWG = 1024;
 constexpr int kBatchLayout = kLayout4x32;
 // The argument-path kernel (at most kSmallBatch requests, mostly a tile or
 // two per wave) keeps the single-buffer kernel's small-message shape: 256
-// threads, two tables x 32 copies (half the fill), rounds 1-2 in full (no
-// group-constant chain of scalar loads ahead of the rounds).
+// threads, two tables x 32 copies (half the fill).
 constexpr int kSmallWG = 256;
 constexpr int kSmallLayout = kLayout2x32;
 
@@ -32,63 +36,12 @@ constexpr int kSmallLayout = kLayout2x32;
 // it, or any launch in flight, writes.
 typedef __attribute__((address_space(4))) const uint32_t c_u32;
 
-// Blocks [b0, b1) of one request.  The loop trip count is the same for every
-// lane (the round-1/2 sharing needs the whole wave), and lane i of each step
-// holds block s0 + 64*b + i.  FULL: rounds 1-2 of every block in full
-// instead of from the wave's group constants.
-template <int NR, int LAYOUT, int BPL, bool FULL>
-__device__ __forceinline__ void run_tile(const TTable<LAYOUT> &tt, const CtrArgs &a, uint64_t b0,
-                                         uint64_t b1, uint32_t lane)
-{
-    const uint64_t nfull = a.len >> 4;
-    const uint32_t tail = static_cast<uint32_t>(a.len & 15);
-    // rotr(rk, 8) of rounds 2..Nr-1 for the two-table fold (the four-table
-    // layout reads none).
-    uint32_t krot[60];
-    if constexpr (LAYOUT != kLayout4x32) {
-#pragma unroll
-        for (int i = 8; i < 4 * NR; ++i) krot[i] = rotr8(a.rk[i]);
-    }
-    for (uint64_t s0 = b0; s0 < b1; s0 += 64 * BPL) {
-        uint32_t ctr[BPL], ks[BPL][4];
-        u32x4 d[BPL];
-#pragma unroll
-        for (int b = 0; b < BPL; ++b) {
-            const uint64_t idx = s0 + 64 * b + lane;
-            ctr[b] = a.ctr0 + static_cast<uint32_t>(idx);
-            if (idx < b1) {
-                if (idx < nfull)
-                    d[b] = load_block(a.in, idx);
-                else
-                    d[b] = load_partial(a.in, nfull, tail);
-            }
-        }
-        if constexpr (FULL) {
-            keystream<NR, LAYOUT, BPL>(tt, a, krot, ctr, ks);
-        } else {
-            const WaveGroups w = wave_groups<BPL>(a, a.ctr0 + static_cast<uint32_t>(s0));
-            keystream_wave<NR, LAYOUT, BPL>(tt, a, krot, ctr, w, ks);
-        }
-#pragma unroll
-        for (int b = 0; b < BPL; ++b) {
-            const uint64_t idx = s0 + 64 * b + lane;
-            if (idx >= b1)
-                continue;
-            const u32x4 v = d[b] ^ u32x4{ks[b][0], ks[b][1], ks[b][2], ks[b][3]};
-            if (idx < nfull)
-                store_block(a.out, idx, v);
-            else
-                store_partial(a.out, nfull, tail, v);
-        }
-    }
-}
-
 // Tile t of request R (a BatchDesc in the device table or a SmallRec in the
 // kernel arguments; both wave-uniform, so their fields arrive by scalar
 // loads) with round keys rk (wave-uniform, read from the launch's inline keys
 // or from a slot of the resident key table): the request's key material and
 // pointers, then the tile's blocks.
-template <int LAYOUT, int BPL, bool FULL, class Rec>
+template <int LAYOUT, int BPL, class Rec>
 __device__ __forceinline__ void request_tile(const TTable<LAYOUT> &tt, const Rec &R, const uint32_t (&rk)[60],
                                              uint32_t t, uint32_t tile_blocks, uint32_t lane)
 {
@@ -106,13 +59,20 @@ __device__ __forceinline__ void request_tile(const TTable<LAYOUT> &tt, const Rec
 #pragma unroll
     for (int i = 0; i < 60; ++i)
         a.rk[i] = i < 44 || nrk > 44 ? rk[i] : 0;
-    const uint64_t nblocks = (a.len + 15) >> 4;
-    const uint64_t b0 = static_cast<uint64_t>(t - R.tile0) * tile_blocks;
-    const uint64_t b1 = b0 + tile_blocks < nblocks ? b0 + tile_blocks : nblocks;
+    const uint64_t positions = message_shift(a.ctr0) + ((a.len + 15) >> 4);
+    const uint64_t p0 = static_cast<uint64_t>(t - R.tile0) * tile_blocks;
+    const uint64_t p1 = p0 + tile_blocks < positions ? p0 + tile_blocks : positions;
+    // rotr(rk, 8) of rounds 2..Nr-1 for the two-table fold (the four-table
+    // layout reads none).
+    uint32_t krot[60];
+    if constexpr (LAYOUT != kLayout4x32) {
+#pragma unroll
+        for (int i = 8; i < 56; ++i) krot[i] = rotr8(a.rk[i]);
+    }
     if (nr == 10)
-        run_tile<10, LAYOUT, BPL, FULL>(tt, a, b0, b1, lane);
+        run_tile<10, LAYOUT, BPL>(tt, a, krot, p0, p1, lane);
     else
-        run_tile<14, LAYOUT, BPL, FULL>(tt, a, b0, b1, lane);
+        run_tile<14, LAYOUT, BPL>(tt, a, krot, p0, p1, lane);
 }
 
 // Writes the round keys of key record `src` (64 words) into slot `slot` of
@@ -135,6 +95,7 @@ __global__ __launch_bounds__(kBatchWG) void ctr_batch_kernel(const uint8_t *__re
 {
     __shared__ uint32_t lds[kLdsWords];
     __shared__ uint32_t s_tile0[kMaxBatch];
+    __shared__ uint32_t s_next;
 
     const BatchHeader *hdr = reinterpret_cast<const BatchHeader *>(table);
     const BatchDesc *desc = reinterpret_cast<const BatchDesc *>(table + sizeof(BatchHeader));
@@ -157,23 +118,54 @@ __global__ __launch_bounds__(kBatchWG) void ctr_batch_kernel(const uint8_t *__re
         }
     }
     fill_write<kBatchLayout, kBatchWG>(lds, tv);
+    if (threadIdx.x == 0)
+        s_next = kBatchWG / 64;    // the waves' first tiles are their own numbers
     __syncthreads();
 
     const uint32_t lane = threadIdx.x & 63;
     TTable<kBatchLayout> tt{reinterpret_cast<const char *>(lds), 4 * (lane & 31), 4 * (lane & 31) | 0x10000u};
 
-    // Tile claiming.  The launch's W waves first take tiles 0..W-1 statically,
-    // spread so that consecutive tiles land on different CUs (wave j of
-    // workgroup b takes tile j * grid + b): a batch of at most W tiles needs
-    // no atomic at all.  Later tiles are claimed from the header counter
-    // (tile = W + counter); a wave issues its next claim when it starts a
-    // tile, so the atomic's round trip hides behind the tile's work.
-    const uint32_t waves = gridDim.x * (kBatchWG / 64);
-    uint32_t t = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * gridDim.x + blockIdx.x;
-    while (t < total) {
-        uint32_t claim = 0;
+    // Tile claiming.  Each workgroup owns hdr->own_tiles tiles, tile k * grid +
+    // b being the k-th of workgroup b, and its waves take the next one from a
+    // counter in LDS (older waves win the issue slots and finish first, so
+    // equal shares per wave would leave the SIMDs to the youngest at the end).
+    // What is left of a large batch after that is claimed from the header's
+    // counter, one ahead of the tile in work: it evens out the CUs.  With a
+    // claim from that counter by every wave at its first tile, 64 requests of
+    // 12 MB in all took 50 us in this kernel; now 20.
+    const uint32_t own = hdr->own_tiles, grid = gridDim.x;
+    auto next_own = [&] {
+        uint32_t k = 0;
         if (lane == 0)
-            claim = atomicAdd(counter, 1u);
+            k = atomicAdd(&s_next, 1u);
+        return static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(k)));
+    };
+    auto claim = [&] {
+        uint32_t k = 0;
+        if (lane == 0)
+            k = atomicAdd(counter, 1u);
+        return k;
+    };
+    uint32_t k = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t claimed = 0;
+    for (bool mine = true;;) {
+        uint32_t t;
+        if (mine) {
+            t = k * grid + blockIdx.x;
+            if (k >= own) {
+                mine = false;
+                if (own * grid >= total)
+                    break;
+                claimed = claim();
+            }
+        }
+        if (!mine) {
+            t = own * grid + __builtin_amdgcn_readfirstlane(claimed);
+            if (t < total)
+                claimed = claim();
+        }
+        if (t >= total)
+            break;
         // Last request whose first tile is <= t (empty requests share their
         // successor's tile0 and are skipped by taking the last match).
         uint32_t lo = 0, hi = n - 1;
@@ -197,8 +189,9 @@ __global__ __launch_bounds__(kBatchWG) void ctr_batch_kernel(const uint8_t *__re
 #pragma unroll
             for (int i = 0; i < 60; ++i) rk[i] = p[i];
         }
-        request_tile<kBatchLayout, BPL, false>(tt, R, rk, t, tile_blocks, lane);
-        t = waves + __builtin_amdgcn_readfirstlane(claim);
+        request_tile<kBatchLayout, BPL>(tt, R, rk, t, tile_blocks, lane);
+        if (mine)
+            k = next_own();
     }
 }
 
@@ -246,7 +239,7 @@ __global__ __launch_bounds__(kSmallWG) void ctr_batch_small_kernel(const SmallBa
 #pragma unroll
             for (int i = 0; i < 60; ++i) rk[i] = R.rk[i];
         }
-        request_tile<kSmallLayout, BPL, true>(tt, R, rk, t, args.tile_blocks, lane);
+        request_tile<kSmallLayout, BPL>(tt, R, rk, t, args.tile_blocks, lane);
     }
 }
 

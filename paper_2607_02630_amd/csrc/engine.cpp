@@ -187,7 +187,7 @@ int launch_batch(aes_engine *e, int s, const std::vector<Req> &batch, std::vecto
         uint64_t tiles = 0;
         const uint64_t tile_blocks = tile / 16;
         for (const BatchDesc &r : e->descs)
-            tiles += ((r.len + 15) / 16 + tile_blocks - 1) / tile_blocks;
+            tiles += aesctr::request_tiles(r.len, r.ctr0, static_cast<uint32_t>(tile_blocks));
         uint64_t grid = tiles < cus ? tiles : cus;
         if (grid < 1)
             grid = 1;
