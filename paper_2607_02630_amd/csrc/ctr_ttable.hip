@@ -98,8 +98,9 @@ __device__ __forceinline__ uint32_t first_ctr(const CtrArgs &a, uint64_t start, 
 // thread behind the rest, byte by byte, it added a block's ten rounds and up
 // to fifteen memory round trips to every launch: AES-128, 70,001 bytes 4.19 ->
 // 3.21 us, 8,000,003 bytes 7.76 -> 7.52; AES-256, 1,000,003 bytes 5.29 -> 3.94.
-// With four blocks per lane its registers cost more than that (133 VGPRs: one
-// workgroup per CU), so those kernels keep the single thread.
+// Built for launches of one chunk per workgroup: where workgroups take several,
+// the last one has fewer and its single thread hides behind the others (AES-256,
+// 3.56 MB in two chunks: 6.82 us, 7.25 with the partial block in its chunk).
 //
 // The scalars come first in the argument list, apart from the key material,
 // so the dispatcher preloads them into SGPRs (the build asks for kernel
@@ -123,7 +124,7 @@ __global__ __launch_bounds__(WG) void ctr_ttable_kernel(const uint8_t *in, uint8
         a.rk[i] = keys.rk[i];
     __shared__ uint32_t lds[layout_lds_words(LAYOUT)];
 
-    const uint64_t nfull = a.len >> 4, nblocks = nfull + TAIL;
+    const uint64_t nfull = a.len >> 4;
     const uint64_t wg = WG;
     const uint64_t step = static_cast<uint64_t>(gridDim.x) * wg * BPL;
     uint64_t start = static_cast<uint64_t>(blockIdx.x) * wg * BPL;
@@ -191,16 +192,20 @@ __global__ __launch_bounds__(WG) void ctr_ttable_kernel(const uint8_t *in, uint8
     // two chunks per trip with the data buffers swapping roles, so no
     // register copy forces an early wait on the loads in flight.
     u32x4 e[BPL];
-    if (start < nblocks) {
+    if constexpr (TAIL) {
+        chunk_step<NR, LAYOUT, BPL, TAIL, FIRST == kFirstFull>(tt, a, krot, start, chunk, wave, lane, nfull, w, d);
+        return;
+    }
+    if (start < nfull) {
         prefetch<BPL>(src, start + step, wave, lane, nfull, last, e);
         chunk_step<NR, LAYOUT, BPL, TAIL, FIRST == kFirstFull>(tt, a, krot, start, chunk, wave, lane, nfull, w, d);
         start += step;
-        while (start < nblocks) {
+        while (start < nfull) {
             prefetch<BPL>(src, start + step, wave, lane, nfull, last, d);
             w = wave_groups<BPL>(a, first_ctr<BPL>(a, start, wave));
             chunk_step<NR, LAYOUT, BPL, TAIL>(tt, a, krot, start, chunk, wave, lane, nfull, w, e);
             start += step;
-            if (!(start < nblocks))
+            if (!(start < nfull))
                 break;
             prefetch<BPL>(src, start + step, wave, lane, nfull, last, e);
             w = wave_groups<BPL>(a, first_ctr<BPL>(a, start, wave));
@@ -209,20 +214,18 @@ __global__ __launch_bounds__(WG) void ctr_ttable_kernel(const uint8_t *in, uint8
         }
     }
 
-    // Final partial block: leading bytes of its keystream block.  Where TAIL
-    // kernels are built no message with one comes here, but without this code
-    // the compiler starts the key material's scalar loads behind the barrier
-    // (1 MiB 3.20 -> 3.29-3.42 us, also with the loads pinned above it).
-    if constexpr (!TAIL) {
-        const uint32_t tail = static_cast<uint32_t>(a.len & 15);
-        if (tail != 0 && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-            uint32_t ctr1[1] = {a.ctr0 + static_cast<uint32_t>(nfull)};
-            uint32_t ks[1][4];
-            keystream<NR, LAYOUT, 1>(tt, a, krot, ctr1, ks);
-            const uint64_t off = 16 * nfull;
-            for (uint32_t i = 0; i < tail; ++i)
-                a.out[off + i] = a.in[off + i] ^ static_cast<uint8_t>(ks[0][i >> 2] >> (8 * (i & 3)));
-        }
+    // Final partial block: leading bytes of its keystream block.  (Byte by
+    // byte: with load_partial here the compiler starts the key material's
+    // scalar loads behind the barrier, and every launch of 1 MiB takes 3.38 us
+    // instead of 3.20.)
+    const uint32_t tail = static_cast<uint32_t>(a.len & 15);
+    if (tail != 0 && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
+        uint32_t ctr1[1] = {a.ctr0 + static_cast<uint32_t>(nfull)};
+        uint32_t ks[1][4];
+        keystream<NR, LAYOUT, 1>(tt, a, krot, ctr1, ks);
+        const uint64_t off = 16 * nfull;
+        for (uint32_t i = 0; i < tail; ++i)
+            a.out[off + i] = a.in[off + i] ^ static_cast<uint8_t>(ks[0][i >> 2] >> (8 * (i & 3)));
     }
 }
 
@@ -232,7 +235,7 @@ int launch_g(const CtrArgs &a, const Shape &sh, hipStream_t st)
     const CtrKeys keys = ctr_keys(a);
     (void)hipGetLastError();   // not ours: left by earlier calls
     if constexpr (BPL <= 2) {
-        if (a.len & 15) {
+        if ((a.len & 15) && static_cast<uint64_t>(sh.grid) * WG * BPL >= (a.len + 15) / 16) {
             hipLaunchKernelGGL((ctr_ttable_kernel<NR, LAYOUT, BPL, WG, FIRST, true>), dim3(sh.grid), dim3(WG), 0, st,
                                a.in, a.out, a.len, a.ctr0, a.x0, keys);
             return launch_status();
