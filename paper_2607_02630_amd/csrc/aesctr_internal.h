@@ -199,6 +199,11 @@ constexpr size_t kMaxTableBytes = batch_table_bytes(kMaxBatch, kMaxBatch, kMaxBa
 
 int launch_ctr_batch(const void *dev_table, int grid, int wg, int bpl, hipStream_t st);
 
+// Copies quads 16-byte pieces from src (pinned host memory's device address) to
+// dst with a kernel; set_upload_node gives a captured one other arguments.
+int launch_upload(const void *src, void *dst, uint32_t quads, hipStream_t st);
+hipError_t set_upload_node(hipGraphExec_t exec, hipGraphNode_t node, const void *src, void *dst, uint32_t quads);
+
 // Small batches (at most kSmallBatch requests) travel in the kernel argument
 // block instead of a device table; each record carries its own round keys
 // (used unless it names a resident slot) and the slot it installs them into,

@@ -4,7 +4,7 @@
 // Per (device, stream) the library keeps a context: a device table (header +
 // up to kMaxBatch descriptors, their inline keys and key installs) and a ring
 // of pinned host staging slots, each with an executable HIP graph of two
-// nodes -- the host-to-device copy of that slot into the table, then the
+// nodes -- the kernel that copies that slot into the table, then the
 // persistent batch kernel.  A call fills a free slot, sets its graph's copy
 // size, and launches the graph on the caller's stream; nothing is
 // re-captured between calls.  A slot (and its graph) is reused only after the
@@ -29,7 +29,7 @@ namespace aesctr {
 namespace {
 
 constexpr int kSlots = 4;
-constexpr size_t kTableBytes = kMaxTableBytes;
+constexpr size_t kTableBytes = (kMaxTableBytes + 15) & ~size_t(15);   // the upload moves whole quads
 
 // Descriptors per part of the host's parallel validation.
 constexpr size_t kCheckGrain = 4096;
@@ -41,7 +41,7 @@ struct BatchShape {
 struct SlotGraph {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    hipGraphNode_t copy_node = nullptr;
+    hipGraphNode_t upload_node = nullptr;
     int grid = 0, bpl = 0;
 };
 
@@ -50,6 +50,7 @@ struct BatchCtx {
     int device = -1;
     void *dev_table = nullptr;
     uint8_t *staging[kSlots] = {};
+    const void *staging_view[kSlots] = {};   // the pinned slots' device addresses
     hipEvent_t done[kSlots] = {};
     bool used[kSlots] = {};
     SlotGraph g[kSlots];
@@ -72,9 +73,16 @@ int init_ctx(BatchCtx *c, int device)
     if (hipMalloc(&c->dev_table, kTableBytes) != hipSuccess)
         return AES_ENOMEM;
     for (int i = 0; i < kSlots; ++i) {
-        if (hipHostMalloc(reinterpret_cast<void **>(&c->staging[i]), kTableBytes, hipHostMallocDefault) !=
+        // Coherent (fine-grained): the upload kernel reads the slot, and a
+        // reused slot must never be served from a line cached by an earlier
+        // launch.
+        if (hipHostMalloc(reinterpret_cast<void **>(&c->staging[i]), kTableBytes, hipHostMallocCoherent) !=
             hipSuccess)
             return AES_ENOMEM;
+        void *view = nullptr;
+        if (hipHostGetDevicePointer(&view, c->staging[i], 0) != hipSuccess || !view)
+            return AES_EDEVICE;
+        c->staging_view[i] = view;
         if (hipEventCreateWithFlags(&c->done[i], hipEventDisableTiming) != hipSuccess)
             return AES_EDEVICE;
     }
@@ -108,7 +116,7 @@ BatchCtx *get_ctx(int device, void *stream, int *rc)
     return c;
 }
 
-// Capture (copy of slot s into the table) + kernel on a private stream.
+// Capture (upload of slot s into the table) + kernel on a private stream.
 int build_graph(BatchCtx *c, int s, int grid, int bpl)
 {
     SlotGraph &sg = c->g[s];
@@ -124,23 +132,18 @@ int build_graph(BatchCtx *c, int s, int grid, int bpl)
     if (hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) != hipSuccess) {
         rc = AES_EDEVICE;
     } else {
-        (void)hipMemcpyAsync(c->dev_table, c->staging[s], kTableBytes, hipMemcpyHostToDevice, cap);
-        int lrc = launch_ctr_batch(c->dev_table, grid, 1024, bpl, cap);
+        int lrc = launch_upload(c->staging_view[s], c->dev_table, kTableBytes / 16, cap);
+        if (lrc == AES_OK)
+            lrc = launch_ctr_batch(c->dev_table, grid, 1024, bpl, cap);
         hipGraph_t g = nullptr;
         if (hipStreamEndCapture(cap, &g) != hipSuccess || lrc != AES_OK || !g) {
             rc = lrc != AES_OK ? lrc : AES_EDEVICE;
         } else {
             sg.graph = g;
-            size_t nn = 0;
-            (void)hipGraphGetNodes(g, nullptr, &nn);
-            std::vector<hipGraphNode_t> nodes(nn);
-            (void)hipGraphGetNodes(g, nodes.data(), &nn);
-            for (hipGraphNode_t nd : nodes) {
-                hipGraphNodeType ty;
-                if (hipGraphNodeGetType(nd, &ty) == hipSuccess && ty == hipGraphNodeTypeMemcpy)
-                    sg.copy_node = nd;
-            }
-            if (!sg.copy_node || hipGraphInstantiate(&sg.exec, g, nullptr, nullptr, 0) != hipSuccess)
+            size_t roots = 1;
+            if (hipGraphGetRootNodes(g, &sg.upload_node, &roots) != hipSuccess || roots != 1)
+                sg.upload_node = nullptr;
+            if (!sg.upload_node || hipGraphInstantiate(&sg.exec, g, nullptr, nullptr, 0) != hipSuccess)
                 rc = AES_EDEVICE;
         }
     }
@@ -265,23 +268,21 @@ int take_slot(BatchCtx *c, int *slot)
 int submit_slot(BatchCtx *c, int slot, size_t bytes, hipStream_t st, int grid, int bpl, bool use_graph)
 {
     int rc;
+    const uint32_t quads = static_cast<uint32_t>((bytes + 15) / 16);
     if (use_graph) {
         SlotGraph &sg = c->g[slot];
         if (!sg.exec || sg.grid != grid || sg.bpl != bpl) {
             if ((rc = build_graph(c, slot, grid, bpl)) != AES_OK)
                 return rc;
         }
-        if (hipGraphExecMemcpyNodeSetParams1D(sg.exec, sg.copy_node, c->dev_table, c->staging[slot], bytes,
-                                              hipMemcpyHostToDevice) != hipSuccess ||
+        if (set_upload_node(sg.exec, sg.upload_node, c->staging_view[slot], c->dev_table, quads) != hipSuccess ||
             hipGraphLaunch(sg.exec, st) != hipSuccess) {
             note_device_error(hipGetLastError());
             return AES_EDEVICE;
         }
     } else {
-        if (hipMemcpyAsync(c->dev_table, c->staging[slot], bytes, hipMemcpyHostToDevice, st) != hipSuccess) {
-            note_device_error(hipGetLastError());
-            return AES_EDEVICE;
-        }
+        if ((rc = launch_upload(c->staging_view[slot], c->dev_table, quads, st)) != AES_OK)
+            return rc;
         if ((rc = launch_ctr_batch(c->dev_table, grid, 1024, bpl, st)) != AES_OK)
             return rc;
     }

@@ -195,6 +195,21 @@ __global__ __launch_bounds__(kBatchWG) void ctr_batch_kernel(const uint8_t *__re
     }
 }
 
+// The upload of a launch table from pinned staging: `quads` 16-byte pieces.  A
+// kernel of the library's own because the copy that the runtime queues ahead of
+// a launch costs more (64 requests, 20 KB of table: 33.4 -> 32.2 us a call; 9 of
+// 4.5 MB 45.5 -> 43.5; an engine's first launch 7.6 -> 1.6 ms).  A table of 1.3 MB
+// takes about 25 us either way, the rate of the PCIe link.
+constexpr int kUploadWG = 256;
+constexpr uint32_t kUploadGrid = 256;
+
+__global__ __launch_bounds__(kUploadWG) void upload_kernel(const u32x4 *__restrict__ src, u32x4 *__restrict__ dst,
+                                                           uint32_t quads)
+{
+    for (uint32_t i = blockIdx.x * kUploadWG + threadIdx.x; i < quads; i += gridDim.x * kUploadWG)
+        dst[i] = src[i];
+}
+
 // A batch of at most kSmallBatch requests whose records travel in the kernel
 // argument block: no descriptor upload goes ahead of the launch (a separate
 // host-to-device copy adds about 20 us to a small batch's latency).  Tiles
@@ -244,6 +259,35 @@ __global__ __launch_bounds__(kSmallWG) void ctr_batch_small_kernel(const SmallBa
 }
 
 }  // namespace
+
+namespace {
+
+uint32_t upload_grid(uint32_t quads)
+{
+    const uint32_t g = (quads + kUploadWG - 1) / kUploadWG;
+    return g < 1 ? 1 : g > kUploadGrid ? kUploadGrid : g;
+}
+
+}  // namespace
+
+int launch_upload(const void *src, void *dst, uint32_t quads, hipStream_t st)
+{
+    (void)hipGetLastError();   // not ours: left by earlier calls
+    hipLaunchKernelGGL(upload_kernel, dim3(upload_grid(quads)), dim3(kUploadWG), 0, st, static_cast<const u32x4 *>(src),
+                       static_cast<u32x4 *>(dst), quads);
+    return launch_status();
+}
+
+hipError_t set_upload_node(hipGraphExec_t exec, hipGraphNode_t node, const void *src, void *dst, uint32_t quads)
+{
+    void *args[3] = {&src, &dst, &quads};
+    hipKernelNodeParams kp{};
+    kp.func = reinterpret_cast<void *>(upload_kernel);
+    kp.gridDim = dim3(upload_grid(quads));
+    kp.blockDim = dim3(kUploadWG);
+    kp.kernelParams = args;
+    return hipGraphExecKernelNodeSetParams(exec, node, &kp);
+}
 
 int launch_ctr_batch(const void *dev_table, int grid, int wg, int bpl, hipStream_t st)
 {
