@@ -519,49 +519,57 @@ __device__ __forceinline__ void lane_consts(const TTable<LAYOUT> &tt, const CtrA
     L[3] = tt.template get<1, 1>(s10);
 }
 
-// Positions [p0, p1) of message a, p0 a multiple of 64, N x 64 of them per
-// step; positions outside the message are left out.  krot: rotr(rk, 8) for the
-// two-table layouts.
+// Positions [p0, p1) of message a, p0 a multiple of 64 and p1 - p0 below 2^31,
+// N x 64 of them per step; positions outside the message are left out.  krot:
+// rotr(rk, 8) for the two-table layouts.
 template <int NR, int LAYOUT, int N>
 __device__ __forceinline__ void run_tile(const TTable<LAYOUT> &tt, const CtrArgs &a, const uint32_t *krot, uint64_t p0,
                                          uint64_t p1, uint32_t lane)
 {
     static_assert(N == 1 || N == 2, "steps of 64 or 128 blocks");
+    // From here on positions count from p0, in 32 bits (the round keys leave
+    // few scalar registers): [lo, hi) are whole blocks of the message, `odd` is
+    // the partial one, if it is in this tile.
     const uint32_t shift = message_shift(a.ctr0);
-    const uint64_t nfull = a.len >> 4;
+    const uint32_t n = static_cast<uint32_t>(p1 - p0);
+    const uint64_t end = (a.len >> 4) + shift;    // position of the partial block
+    const uint32_t lo = p0 == 0 ? shift : 0;
+    const uint32_t hi = end < p1 ? static_cast<uint32_t>(end - p0) : n;
     const uint32_t tail = static_cast<uint32_t>(a.len & 15);
-    const uint32_t first = a.ctr0 - shift + static_cast<uint32_t>(p0);    // counter of position p0
+    const uint32_t odd = tail != 0 && end < p1 ? hi : ~0u;
+    const int64_t base = 16 * (static_cast<int64_t>(p0) - shift);
+    const uint8_t *in = a.in + base;
+    uint8_t *out = a.out + base;
+    const uint32_t first = a.ctr0 - shift + static_cast<uint32_t>(p0);    // counter of position 0
+
+    u32x4 part = {0, 0, 0, 0};
+    if (odd != ~0u)
+        part = load_partial(in, odd, tail);
     uint32_t L[4][4];
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-        if (p0 + 64 * k < p1)
+        if (64u * k < n)
             lane_consts(tt, a, first + 64 * k + lane, L[k]);
     uint32_t Gv[4];
-    uint32_t window = ~0u;    // the 64 groups whose constants Gv holds, counted from p0's
-    auto step = [&](uint64_t p, const uint32_t (*Lk)[4]) {
-        const int64_t j0 = static_cast<int64_t>(p) - shift;
-        const bool whole = j0 >= 0 && j0 + 64 * N <= static_cast<int64_t>(nfull) && p + 64 * N <= p1;
-        const uint8_t *in = a.in + 16 * j0;
-        uint8_t *out = a.out + 16 * j0;
+    uint32_t window = ~0u;    // the 64 groups whose constants Gv holds, counted from position 0's
+    auto step = [&](uint32_t q, const uint32_t (*Lk)[4]) {
+        const bool whole = q >= lo && q + 64 * N <= hi;
         u32x4 d[N];
         if (whole) {
 #pragma unroll
-            for (int b = 0; b < N; ++b) d[b] = load_block(in, 64 * b + lane);
+            for (int b = 0; b < N; ++b) d[b] = load_block(in, q + 64 * b + lane);
         } else {
 #pragma unroll
             for (int b = 0; b < N; ++b) {
-                const uint64_t j = static_cast<uint64_t>(j0 + 64 * b + lane);    // above nfull when before the message
-                const bool mine = p + 64 * b < p1;
-                if (mine && j < nfull)
-                    d[b] = load_block(in, 64 * b + lane);
-                else if (mine && j == nfull && tail != 0)
-                    d[b] = load_partial(a.in, nfull, tail);
+                const uint32_t i = q + 64 * b + lane;
+                if (i >= lo && i < hi)
+                    d[b] = load_block(in, i);
             }
         }
         uint32_t s[N][4], o[N][4];
 #pragma unroll
         for (int b = 0; b < N; ++b) {
-            const uint32_t g = ((first & 255u) + static_cast<uint32_t>(p - p0) + 64 * b) >> 8;
+            const uint32_t g = ((first & 255u) + q + 64 * b) >> 8;
             if ((g >> 6) != window) {
                 window = g >> 6;
                 group_consts_lds(tt, a, ((first >> 8) + (window << 6) + lane) & 0xffffffu, Gv);
@@ -583,33 +591,33 @@ __device__ __forceinline__ void run_tile(const TTable<LAYOUT> &tt, const CtrArgs
 #pragma unroll
         for (int b = 0; b < N; ++b)
             tt.last_round(s[b], o[b], &a.rk[4 * NR]);
-#pragma unroll
-        for (int b = 0; b < N; ++b)
-            d[b] ^= u32x4{o[b][0], o[b][1], o[b][2], o[b][3]};
         if (whole) {
 #pragma unroll
-            for (int b = 0; b < N; ++b) store_block(out, 64 * b + lane, d[b]);
+            for (int b = 0; b < N; ++b)
+                store_block(out, q + 64 * b + lane, d[b] ^ u32x4{o[b][0], o[b][1], o[b][2], o[b][3]});
         } else {
 #pragma unroll
             for (int b = 0; b < N; ++b) {
-                const uint64_t j = static_cast<uint64_t>(j0 + 64 * b + lane);
-                const bool mine = p + 64 * b < p1;
-                if (mine && j < nfull)
-                    store_block(out, 64 * b + lane, d[b]);
-                else if (mine && j == nfull && tail != 0)
-                    store_partial(a.out, nfull, tail, d[b]);
+                const uint32_t i = q + 64 * b + lane;
+                const u32x4 ks = {o[b][0], o[b][1], o[b][2], o[b][3]};
+                if (i >= lo && i < hi)
+                    store_block(out, i, d[b] ^ ks);
+                if (i == odd)
+                    part ^= ks;
             }
         }
     };
-    for (uint64_t p = p0; p < p1;) {
+    for (uint32_t q = 0; q < n;) {
 #pragma unroll
         for (int k = 0; k < 4; k += N) {
-            step(p, &L[k]);
-            p += 64 * N;
-            if (p >= p1)
+            step(q, &L[k]);
+            q += 64 * N;
+            if (q >= n)
                 break;
         }
     }
+    if (odd != ~0u && lane == (odd & 63))
+        store_partial(out, odd, tail, part);
 }
 
 }  // namespace
