@@ -108,6 +108,10 @@ int check_buffers(const void *in, const void *out, uint64_t len);
 
 // Launchers (return AES_OK or AES_EDEVICE).
 int launch_ctr_ttable(const CtrArgs &a, int nr, const Shape &sh, hipStream_t st);
+// Whether a T-table shape (four tables x 32 copies, 1024 threads, two blocks per
+// lane) with this much work runs as ctr_bulk.hip's kernel, and its launch.
+bool bulk_shape(const Shape &sh, uint64_t len);
+int launch_ctr_bulk(const CtrArgs &a, int nr, const Shape &sh, hipStream_t st);
 int launch_ctr_bitslice(const CtrArgs &a, int nr, const Shape &sh, hipStream_t st);
 
 // Arguments of the vector-permute kernel (ctr_vperm.hip): the round keys in

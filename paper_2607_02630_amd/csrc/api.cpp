@@ -126,11 +126,24 @@ Shape default_shape(int variant, int key_bits, uint64_t len, const DeviceInfo &d
         // to 1 MiB (1 MiB AES-128 3.32 against 3.65 us) and 2-3% at 2-4 MiB.
         // From 8 MiB 512 threads x 2 blocks (x 4 from 16 MiB) with up to
         // four workgroups per CU in the grid, two of them resident at a time.
+        // From 16 MiB on that shape takes steps of a chunk per CU (32 KiB x
+        // CUs), so it stays only where chunks are a whole number per CU, up to
+        // 32 MiB; else one persistent workgroup per CU (ctr_bulk.hip), whose
+        // waves share 4 KiB tiles.  AES-128: 16 MiB 12.9 us (bulk 13.5), 16 MiB +
+        // 100 bytes 17.6 (13.6), 24 MiB 18.0 (19.1), 32 MiB 23.0 (23.2), 48 MiB
+        // 35.2 (31.1), 96.3 MiB 70.6 (60.4), 256 MiB 167 (153); AES-256: 16 MiB
+        // 17.3 (17.7), 32 MiB 30.6 (31.6), 48 MiB 47.6 (42.7), 256 MiB 230 (208).
         sh.grid = di.num_cus;
         sh.copies = 32;
         sh.tables = 2;
         const uint64_t per_cu = (len / 16) / static_cast<uint64_t>(di.num_cus > 0 ? di.num_cus : 1);
-        if (per_cu >= 2048) {
+        const uint64_t chunks = (len / 16 + 2047) / 2048;    // of 512 threads x 4 blocks
+        if (per_cu >= 4096 && (per_cu > 8192 || chunks % static_cast<uint64_t>(di.num_cus) != 0)) {
+            sh.bpl = 2;
+            sh.wg = 1024;
+            sh.tables = 4;
+            sh.wave_groups = kFirstWave0;
+        } else if (per_cu >= 2048) {
             sh.bpl = per_cu >= 4096 ? 4 : 2;
             sh.wg = 512;
             sh.grid = 4 * di.num_cus;
@@ -343,6 +356,8 @@ extern "C" int aes_ctr_crypt_cfg(const aes_sched_t *sched, const uint8_t nonce[1
     memcpy(a.rk, km.rk, sizeof(a.rk));
     if (sh.variant == AES_VARIANT_BITSLICE)
         return launch_ctr_bitslice(a, km.nr, sh, st);
+    if (bulk_shape(sh, len))
+        return launch_ctr_bulk(a, km.nr, sh, st);
     return launch_ctr_ttable(a, km.nr, sh, st);
 }
 

@@ -17,7 +17,7 @@
 // 2.0-2.1 GHz the card holds under this load (2.4 without the payload traffic).
 #include <stddef.h>
 
-#include "ttable_device.h"
+#include "ttable_tile.h"
 
 namespace aesctr {
 namespace {
