@@ -90,13 +90,31 @@ int check_buffers(const void *in, const void *out, uint64_t len)
     return AES_OK;
 }
 
+namespace {
+
+// Whether a tuned T-table entry speaks for a message of this many blocks: its
+// grid takes it in as many chunks as it took the size it was timed at.  Above
+// that another shape may be better by a whole chunk (1.1 MiB in the shape tuned
+// at 1 MiB: 5.00 us, in the rule's 3.65).
+bool tuned_for(const TuneEntry &te, uint64_t blocks, uint64_t cus)
+{
+    const uint64_t pass = static_cast<uint64_t>(te.wg) * te.bpl * te.grid_per_cu * cus;
+    const uint64_t tuned = ((uint64_t(1) << te.size_log2) + 15) / 16;
+    return (blocks + pass - 1) / pass <= (tuned + pass - 1) / pass;
+}
+
+}  // namespace
+
 Shape default_shape(int variant, int key_bits, uint64_t len, const DeviceInfo &di)
 {
     Shape sh{};
     sh.variant = variant == AES_VARIANT_AUTO ? AES_VARIANT_TTABLE : variant;
     sh.wave_groups = -1;    // first-chunk mode: the rule's (resolve_shape)
     TuneEntry te;
-    if (tune_lookup(sh.variant, key_bits, len, &te)) {
+    const uint64_t cus = static_cast<uint64_t>(di.num_cus > 0 ? di.num_cus : 1);
+    const uint64_t blocks = (len + 15) / 16;
+    if (tune_lookup(sh.variant, key_bits, len, &te) &&
+        (sh.variant != AES_VARIANT_TTABLE || tuned_for(te, blocks, cus))) {
         sh.bpl = te.bpl;
         sh.wg = te.wg;
         sh.copies = te.copies;
@@ -109,23 +127,23 @@ Shape default_shape(int variant, int key_bits, uint64_t len, const DeviceInfo &d
         // The LDS holds only T0 and T2 (32 copies, 64 KiB): half the table
         // fill of four tables, for about 15% more VALU work per block, and
         // room for two workgroups per CU, so one workgroup's fill and
-        // barriers overlap the other's keystream.  The chunk a workgroup
-        // takes per step (workgroup size x blocks per lane) is the largest
-        // that still gives every CU work: a larger chunk leaves CUs idle, a
-        // smaller one adds steps.  Measured on MI355X (kernel-only, per
-        // launch, against one workgroup per CU with four tables):
-        //   AES-128  1 MiB 3.72 us (4.04), 8 MiB 7.84 (8.22), 32 MiB 23.5
-        //            (26.6), 256 MiB 172.6 (174.9);
-        //   AES-256  1 MiB 4.11 us (4.57, 256 threads), 8 MiB 9.81 (10.19),
-        //            32 MiB 30.9 (37.0), 256 MiB 242 (246).
-        // Up to 4 MiB one workgroup per CU, each running one chunk, whose
-        // rounds 1-2 run in full (first-chunk mode 2: no group constants, no
-        // second barrier): 256 threads x 1 block up to 1 MiB, 512 x 1 at
-        // 2 MiB, 512 x 2 at 4 MiB.  The autotuner's runs put that 6-10%
-        // ahead of 512 threads with wave 0 computing the group constants up
-        // to 1 MiB (1 MiB AES-128 3.32 against 3.65 us) and 2-3% at 2-4 MiB.
-        // From 8 MiB 512 threads x 2 blocks (x 4 from 16 MiB) with up to
-        // four workgroups per CU in the grid, two of them resident at a time.
+        // barriers overlap the other's keystream.  Time goes in steps: a
+        // workgroup's chunk (workgroup size x blocks per lane) takes as long
+        // full or nearly empty, so the shape is the one whose chunks fill the
+        // CUs best, in blocks per CU.  us per launch at the ends of each range
+        // (AES-128; in brackets the neighbouring shape there):
+        //   up to 256   256 threads x 1 block      4 KiB 2.8, 1 MiB 3.26
+        //   up to 512   512 x 1              1.1 MiB 3.65 (5.00), 2 MiB 3.62 (5.21)
+        //   up to 1024  512 x 2              2.2 MiB 5.07 (5.52), 4 MiB 5.17 (6.24)
+        //   up to 1536  512 x 1, two per CU  4.3 MiB 6.42 (8.30), 6 MiB 6.42 (7.36)
+        //   up to 2048  512 x 2, two per CU  6.8 MiB 7.57 (8.23), 8 MiB 7.65 (8.14)
+        //   up to 2560  512 x 1, two per CU  8.2 MiB 8.71 (9.29), 9.8 MiB 9.10 (9.51)
+        //   up to 3072  512 x 2, two per CU  11.7 MiB 9.77 (10.48)
+        //   below 4096  512 x 2, four per CU 13.7 MiB 12.92 (13.33)
+        // and 512 x 4, four per CU, from 16 MiB.  AES-256 has the same order.
+        // Where every workgroup has one chunk (up to 1024), and with one block
+        // per lane, rounds 1-2 of the first chunk run in full (first-chunk mode
+        // 2: no group constants, no second barrier).
         // From 16 MiB on that shape takes steps of a chunk per CU (32 KiB x
         // CUs), so it stays only where chunks are a whole number per CU, up to
         // 32 MiB; else one persistent workgroup per CU (ctr_bulk.hip), whose
@@ -136,26 +154,29 @@ Shape default_shape(int variant, int key_bits, uint64_t len, const DeviceInfo &d
         sh.grid = di.num_cus;
         sh.copies = 32;
         sh.tables = 2;
-        const uint64_t per_cu = (len / 16) / static_cast<uint64_t>(di.num_cus > 0 ? di.num_cus : 1);
-        const uint64_t chunks = (len / 16 + 2047) / 2048;    // of 512 threads x 4 blocks
-        if (per_cu >= 4096 && (per_cu > 8192 || chunks % static_cast<uint64_t>(di.num_cus) != 0)) {
+        sh.wg = 512;
+        const uint64_t per_cu = (blocks + cus - 1) / cus;
+        const uint64_t chunks = (blocks + 2047) / 2048;    // of 512 threads x 4 blocks
+        if (per_cu <= 1024) {
+            sh.bpl = per_cu > 512 ? 2 : 1;
+            sh.wg = per_cu > 256 ? 512 : 256;
+            sh.wave_groups = kFirstFull;
+        } else if (per_cu <= 1536 || (per_cu > 2048 && per_cu <= 2560)) {
+            sh.bpl = 1;
+            sh.grid = 2 * di.num_cus;
+            sh.wave_groups = kFirstFull;
+        } else if (per_cu < 4096) {
+            sh.bpl = 2;
+            sh.grid = (per_cu <= 3072 ? 2 : 4) * di.num_cus;
+            sh.wave_groups = kFirstPerWave;
+        } else if (per_cu <= 8192 && chunks % cus == 0) {
+            sh.bpl = 4;
+            sh.grid = 4 * di.num_cus;
+        } else {
             sh.bpl = 2;
             sh.wg = 1024;
             sh.tables = 4;
             sh.wave_groups = kFirstWave0;
-        } else if (per_cu >= 2048) {
-            sh.bpl = per_cu >= 4096 ? 4 : 2;
-            sh.wg = 512;
-            sh.grid = 4 * di.num_cus;
-        } else {
-            if (per_cu >= 1024) {
-                sh.bpl = 2; sh.wg = 512;
-            } else if (per_cu >= 512) {
-                sh.bpl = 1; sh.wg = 512;
-            } else {
-                sh.bpl = 1; sh.wg = 256;
-            }
-            sh.wave_groups = kFirstFull;
         }
     } else if (sh.variant == AES_VARIANT_BITSLICE) {
         sh.bpl = 1;
@@ -249,6 +270,7 @@ int check_cfg(const aes_launch_cfg_t *cfg, int *variant)
 Shape resolve_shape(int variant, int key_bits, uint64_t len, const aes_launch_cfg_t *cfg, const DeviceInfo &di)
 {
     Shape sh = default_shape(variant, key_bits, len, di);
+    const Shape def = sh;
     if (cfg) {
         if (cfg->blocks_per_lane) sh.bpl = cfg->blocks_per_lane;
         if (cfg->wg_size) sh.wg = cfg->wg_size;
@@ -275,7 +297,10 @@ Shape resolve_shape(int variant, int key_bits, uint64_t len, const aes_launch_cf
     // Per-wave first-chunk group constants pay off when two workgroups with
     // the 64 KiB image share each CU (8 MiB AES-128: 7.64-7.69 against
     // 7.74-7.78 us); other shapes fall back to wave 0 computing them.
-    const int tuned = sh.wave_groups;
+    // The default's mode holds for its own chunks; with one workgroup per CU it
+    // also stays where cfg changes them.
+    const bool same = sh.bpl == def.bpl && sh.wg == def.wg && sh.tables == def.tables;
+    const int tuned = same || def.grid <= di.num_cus ? def.wave_groups : -1;
     sh.wave_groups = kFirstWave0;
     if (sh.variant == AES_VARIANT_TTABLE) {
         if (cfg && cfg->wave_groups)

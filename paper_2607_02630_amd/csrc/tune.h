@@ -11,7 +11,8 @@
 // "max_tile_bytes" (the tile sizing rule's constants) and "bpl".
 // A lookup takes the entry of the same variant and key size whose size_log2
 // equals floor(log2(len)); a size the tuner did not time has no entry and
-// keeps the built-in rule.
+// keeps the built-in rule, and so does a T-table message that needs more chunks
+// than the tuned size did (default_shape).
 #pragma once
 
 #include <stdint.h>
