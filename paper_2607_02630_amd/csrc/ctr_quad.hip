@@ -4,26 +4,31 @@
 // so its time is the chain of one block's rounds.  Here a quad of lanes holds a
 // block, lane c column c: a round is 4 lookups, 4 address operations, 3 DPP moves
 // and 2 XORs per lane, where one lane per block (ctr_ttable.hip) does 16 lookups
-// and 28 VALU instructions in a row.  A workgroup is one wave with one copy of the
-// four round tables (4 KiB of LDS): the random lookups of a wave meet in the banks
-// three or four deep, which costs less here than filling 64 KiB of copies.
-// (Sixteen waves of quads over 64 KiB of copies: 2.68 us at 4 KiB and 3.16 us at
-// 512 KiB, between the two everywhere, so not kept.)
+// and 28 VALU instructions in a row.  A workgroup is four waves with one copy of
+// the four round tables (4 KiB of LDS, a table per wave to write): the random
+// lookups of a wave meet in the banks about three deep, which costs less here
+// than filling 64 KiB of copies.  (Sixteen waves of quads over 64 KiB of copies:
+// 2.68 us at 4 KiB and 3.16 us at 512 KiB.)
+//
+// The keys reach the lanes through LDS (key_word), and the message is asked for
+// behind the table's stores: no wait of the fill then covers it, and the table
+// reads of 2048 waves don't queue behind it.  The keys loaded per lane from the
+// argument block and the message first, one wave per workgroup: 2.57 us at 256
+// KiB, 2.96 us at 512 KiB; keys through LDS and the message last: 2.16, 2.80; four
+// waves per workgroup: 2.07, 2.44 (and 1.90 instead of 1.80 at 16 bytes).
 // Measured per launch in a replayed graph, AES-128, against one lane per block:
-// 4 KiB 1.93 us (2.89), 64 KiB 2.08 (3.08), 256 KiB 2.60 (3.14), 512 KiB 2.96 (3.19);
-// AES-256: 2.35 (3.40), 2.58 (3.58), 2.82 (3.63), 3.31 (3.71).  An empty launch takes
-// 1.56 us there; the rest is the table and message reads and the chain of rounds.
+// 4 KiB 1.92 us (2.89), 64 KiB 2.02 (3.08), 256 KiB 2.07 (3.14), 512 KiB 2.44 (3.19);
+// AES-256: 2.13 (3.40), 2.21 (3.58), 2.29 (3.63), 2.80 (3.71).  An empty launch takes
+// 1.56 us there.
 #include "ttable_device.h"
 
 namespace aesctr {
 namespace {
 
-// The key material as the lanes read it, a column each, from the kernel's
-// argument block (CtrKeys lies behind the scalars).
-constexpr size_t kKeysOffset = 32;
-typedef const __attribute__((address_space(4))) uint32_t c_u32;
+constexpr uint32_t kQuadWG = 256;
+constexpr uint32_t kBlocks = kQuadWG / 4;   // per workgroup
 
-constexpr uint32_t kBlocks = 16;   // per wave, which is a workgroup
+__constant__ uint32_t g_dummy;   // for the loads of a message of less than a word
 
 template <int CTRL>
 __device__ __forceinline__ uint32_t quad(uint32_t v)
@@ -32,43 +37,45 @@ __device__ __forceinline__ uint32_t quad(uint32_t v)
 }
 
 template <int NR>
-__global__ __launch_bounds__(64) void ctr_quad_kernel(const uint8_t *in, uint8_t *out, uint64_t len, uint32_t ctr0,
-                                                      uint32_t x0, const CtrKeys keys)
+__global__ __launch_bounds__(kQuadWG) void ctr_quad_kernel(const uint8_t *in, uint8_t *out, uint64_t len, uint32_t ctr0,
+                                                           uint32_t x0, const CtrKeys keys)
 {
-    static_assert(sizeof(void *) * 2 + sizeof(uint64_t) + 2 * sizeof(uint32_t) == kKeysOffset, "argument layout");
     __shared__ uint32_t lds[4 * 256];   // table t at word 256 t
-    const uint32_t lane = threadIdx.x, c = lane & 3;
+    __shared__ uint32_t lkeys[kQuadWG];
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane & 3;
     const u32x4 t0 = reinterpret_cast<const u32x4 *>(c_round.t[0])[lane];
+    const uint32_t kw = key_word(lane);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // Table `wave`: T0 rotated.  Each wave keeps the keys for itself.
+    u32x4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_alignbit(t0[i], t0[i], (32 - 8 * wave) & 31);
+    *reinterpret_cast<u32x4 *>(&lds[256 * wave + 4 * lane]) = v;
+    lkeys[threadIdx.x] = kw;
+    __builtin_amdgcn_sched_barrier(0);
 
     // This lane's word of its block; of the last, partial block the bytes there are.
-    const uint64_t blk = static_cast<uint64_t>(blockIdx.x) * kBlocks + (lane >> 2);
+    const uint64_t blk = static_cast<uint64_t>(blockIdx.x) * kBlocks + (threadIdx.x >> 2);
     const uint64_t at = 16 * blk + 4 * c;
     const uint32_t have = at + 4 <= len ? 4 : at < len ? static_cast<uint32_t>(len - at) : 0;
     g_cu8 *src = (g_cu8 *)in + at;
-    uint32_t d = 0;
-    if (have == 4) {
-        d = __builtin_nontemporal_load((g_cu32 *)src);
-    } else {
+    g_cu8 *whole = len >= 4 ? (g_cu8 *)in + (have == 4 ? at : 0) : (g_cu8 *)&g_dummy;
+    uint32_t d = __builtin_nontemporal_load((g_cu32 *)whole);
+    __syncthreads();
+
+    const uint32_t *ks = lkeys + 64 * wave + c;
+    const uint32_t k1 = ks[0];
+    uint32_t rk[NR + 1];
+#pragma unroll
+    for (int r = 2; r <= NR; ++r) rk[r] = ks[4 + 4 * r];
+    if (have < 4) {
+        d = 0;
 #pragma unroll
         for (uint32_t i = 0; i < 3; ++i)
             if (i < have)
                 d |= static_cast<uint32_t>(src[i]) << (8 * i);
     }
-    c_u32 *kp = (c_u32 *)((const __attribute__((address_space(4))) char *)__builtin_amdgcn_kernarg_segment_ptr() +
-                          kKeysOffset) + c;
-    const uint32_t k1 = kp[0];
-    uint32_t rk[NR + 1];
-#pragma unroll
-    for (int r = 2; r <= NR; ++r) rk[r] = kp[4 + 4 * r];
-
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        u32x4 v;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_alignbit(t0[i], t0[i], (32 - 8 * t) & 31);
-        *reinterpret_cast<u32x4 *>(&lds[256 * t + 4 * lane]) = v;
-    }
-    __syncthreads();
 
     // Rounds 0 and 1: column c takes byte 3 - c of the counter column.
     const uint32_t ctr = ctr0 + static_cast<uint32_t>(blk);
@@ -102,17 +109,16 @@ void launch_quad(const CtrArgs &a, hipStream_t st)
 {
     const uint64_t blocks = (a.len + 15) / 16;
     const dim3 grid(static_cast<uint32_t>((blocks + kBlocks - 1) / kBlocks));
-    hipLaunchKernelGGL(ctr_quad_kernel<NR>, grid, dim3(64), 0, st, a.in, a.out, a.len, a.ctr0, a.x0, ctr_keys(a));
+    hipLaunchKernelGGL(ctr_quad_kernel<NR>, grid, dim3(kQuadWG), 0, st, a.in, a.out, a.len, a.ctr0, a.x0, ctr_keys(a));
 }
 
 }  // namespace
 
-// Up to 128 blocks per CU (512 KiB on 256 CUs), two waves of quads per SIMD: from
+// Up to 128 blocks per CU (512 KiB on 256 CUs), two workgroups of quads: from
 // there the bank conflicts of the one table copy cost what the shorter chain
-// saves.  Quads against one lane per block, AES-128 and AES-256: 512 KiB 2.96 us
-// against 3.19 and 3.31 against 3.71; 700,001 bytes 3.28 against 3.29 and 3.81
-// against 3.73; 1 MiB 3.82 against 3.26 and 4.52 against 3.80.  A grid that is
-// smaller than the work is the caller's choice and is kept.
+// saves.  Quads against one lane per block, AES-128 and AES-256: 512 KiB 2.44 us
+// against 3.19 and 2.80 against 3.71; 1 MiB 3.28 against 3.26 and 4.02 against 3.81.
+// A grid that is smaller than the work is the caller's choice and is kept.
 bool quad_shape(const Shape &sh, uint64_t len, int num_cus)
 {
     const uint64_t blocks = (len + 15) / 16;
