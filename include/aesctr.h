@@ -132,10 +132,10 @@ typedef enum {
  *                    shape is not built for is AES_EINVAL.  Output (from
  *                    aes_ctr_launch_shape): the mode used, 1, 2, or 0 for
  *                    wave 0.
- * A message of at most 128 blocks of 16 bytes per CU whose shape is 256 threads,
+ * A message of at most 256 blocks of 16 bytes per CU whose shape is 256 threads,
  * 1 block per lane, 2 tables of 32 copies, mode 2 and a grid that holds it in one
- * chunk per workgroup runs with four lanes per block, in workgroups of one wave
- * and as many as it needs. */
+ * chunk per workgroup runs with four (up to 128 blocks per CU) or two lanes per
+ * block, in workgroups of 256 or 512 threads and as many as it needs. */
 typedef struct {
     int32_t variant;
     int32_t blocks_per_lane;

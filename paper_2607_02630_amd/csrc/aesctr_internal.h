@@ -114,9 +114,12 @@ bool bulk_shape(const Shape &sh, uint64_t len);
 int launch_ctr_bulk(const CtrArgs &a, int nr, const Shape &sh, hipStream_t st);
 // Whether a T-table shape (two tables x 32 copies, 256 threads, one block per
 // lane, first chunk in full, one chunk per workgroup) with this little work runs as
-// ctr_quad.hip's kernel, and its launch (a grid of its own).
+// ctr_quad.hip's or ctr_pair.hip's kernel (asked in this order), and their
+// launches (grids of their own).
 bool quad_shape(const Shape &sh, uint64_t len, int num_cus);
 int launch_ctr_quad(const CtrArgs &a, int nr, hipStream_t st);
+bool pair_shape(const Shape &sh, uint64_t len, int num_cus);
+int launch_ctr_pair(const CtrArgs &a, int nr, hipStream_t st);
 int launch_ctr_bitslice(const CtrArgs &a, int nr, const Shape &sh, hipStream_t st);
 
 // Arguments of the vector-permute kernel (ctr_vperm.hip): the round keys in

@@ -383,6 +383,8 @@ extern "C" int aes_ctr_crypt_cfg(const aes_sched_t *sched, const uint8_t nonce[1
         return launch_ctr_bitslice(a, km.nr, sh, st);
     if (quad_shape(sh, len, di.num_cus))
         return launch_ctr_quad(a, km.nr, st);
+    if (pair_shape(sh, len, di.num_cus))
+        return launch_ctr_pair(a, km.nr, st);
     if (bulk_shape(sh, len))
         return launch_ctr_bulk(a, km.nr, sh, st);
     return launch_ctr_ttable(a, km.nr, sh, st);
