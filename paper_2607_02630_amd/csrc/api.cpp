@@ -132,7 +132,9 @@ Shape default_shape(int variant, int key_bits, uint64_t len, const DeviceInfo &d
         // full or nearly empty, so the shape is the one whose chunks fill the
         // CUs best, in blocks per CU.  us per launch at the ends of each range
         // (AES-128; in brackets the neighbouring shape there):
-        //   up to 256   256 threads x 1 block      4 KiB 2.8, 1 MiB 3.26
+        //   up to 256   256 threads x 1 block, run as four lanes per block up to 128
+        //               (ctr_quad.hip) and as two above (ctr_pair.hip):
+        //                                    4 KiB 1.9, 512 KiB 2.4, 1 MiB 2.8
         //   up to 512   512 x 1              1.1 MiB 3.65 (5.00), 2 MiB 3.62 (5.21)
         //   up to 1024  512 x 2              2.2 MiB 5.07 (5.52), 4 MiB 5.17 (6.24)
         //   up to 1536  512 x 1, two per CU  4.3 MiB 6.42 (8.30), 6 MiB 6.42 (7.36)

@@ -12,7 +12,7 @@
 // AES-256 mixed) and alignment share the launch; dynamic claiming balances
 // the log-uniform size mix.
 //
-// Bound: 4.5 GB in 4096 requests takes 3.1 ms at 128 (AES-128) or 192 table
+// Bound: 4.5 GB in 4096 requests takes 3.0 ms at 128 (AES-128) or 192 table
 // lookups per block, 27 of the 28.6 per clock and CU that the LDS gives, at the
 // 2.0-2.1 GHz the card holds under this load (2.4 without the payload traffic).
 #include <stddef.h>

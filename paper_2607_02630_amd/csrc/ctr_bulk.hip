@@ -16,7 +16,7 @@
 // GHz the card holds under this load (2.4 without the payload traffic).
 // Measured: 256 MiB AES-128 153 us = 1755 GB/s (167 before, two 512-thread
 // workgroups with equal shares per CU), AES-256 208 us = 1290 GB/s (230); ragged
-// 100 MB AES-256 in place 75 us (88).
+// 100 MB AES-256 in place 80 us (89).
 #include "ttable_tile.h"
 
 namespace aesctr {
