@@ -19,7 +19,8 @@
 // Measured per launch in a replayed graph, AES-128, against one lane per block:
 // 4 KiB 1.92 us (2.89), 64 KiB 2.02 (3.08), 256 KiB 2.07 (3.14), 512 KiB 2.44 (3.19);
 // AES-256: 2.13 (3.40), 2.21 (3.58), 2.29 (3.63), 2.80 (3.71).  An empty launch takes
-// 1.56 us there.
+// 1.56 us there.  Batches of a few small requests take the same path
+// (ctr_quad_batch_kernel; figures at launch_small in batch.cpp).
 #include "ttable_device.h"
 
 namespace aesctr {
@@ -27,6 +28,7 @@ namespace {
 
 constexpr uint32_t kQuadWG = 256;
 constexpr uint32_t kBlocks = kQuadWG / 4;   // per workgroup
+static_assert(kBlocks == kQuadTileBlocks, "the tile of a small batch");
 
 __constant__ uint32_t g_dummy;   // for the loads of a message of less than a word
 
@@ -36,49 +38,64 @@ __device__ __forceinline__ uint32_t quad(uint32_t v)
     return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), CTRL, 0xf, 0xf, true));
 }
 
-template <int NR>
-__global__ __launch_bounds__(kQuadWG) void ctr_quad_kernel(const uint8_t *in, uint8_t *out, uint64_t len, uint32_t ctr0,
-                                                           uint32_t x0, const CtrKeys keys)
+// The table of this wave from T0's entries 4 lane .. 4 lane + 3: T0 rotated.
+__device__ __forceinline__ void quad_fill(uint32_t *lds, u32x4 t0, uint32_t wave, uint32_t lane)
 {
-    __shared__ uint32_t lds[4 * 256];   // table t at word 256 t
-    __shared__ uint32_t lkeys[kQuadWG];
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane & 3;
-    const u32x4 t0 = reinterpret_cast<const u32x4 *>(c_round.t[0])[lane];
-    const uint32_t kw = key_word(lane);
-    __builtin_amdgcn_sched_barrier(0);
-
-    // Table `wave`: T0 rotated.  Each wave keeps the keys for itself.
     u32x4 v;
 #pragma unroll
     for (int i = 0; i < 4; ++i) v[i] = __builtin_amdgcn_alignbit(t0[i], t0[i], (32 - 8 * wave) & 31);
     *reinterpret_cast<u32x4 *>(&lds[256 * wave + 4 * lane]) = v;
-    lkeys[threadIdx.x] = kw;
-    __builtin_amdgcn_sched_barrier(0);
+}
 
-    // This lane's word of its block; of the last, partial block the bytes there are.
-    const uint64_t blk = static_cast<uint64_t>(blockIdx.x) * kBlocks + (threadIdx.x >> 2);
-    const uint64_t at = 16 * blk + 4 * c;
-    const uint32_t have = at + 4 <= len ? 4 : at < len ? static_cast<uint32_t>(len - at) : 0;
-    g_cu8 *src = (g_cu8 *)in + at;
-    g_cu8 *whole = len >= 4 ? (g_cu8 *)in + (have == 4 ? at : 0) : (g_cu8 *)&g_dummy;
-    uint32_t d = __builtin_nontemporal_load((g_cu32 *)whole);
-    __syncthreads();
+// Bytes that this lane has of its word at byte `at` of a message of len, and the
+// word if it has all of it; the loads of the other lanes go to valid memory.
+__device__ __forceinline__ uint32_t quad_have(uint64_t at, uint64_t len)
+{
+    return at + 4 <= len ? 4 : at < len ? static_cast<uint32_t>(len - at) : 0;
+}
 
-    const uint32_t *ks = lkeys + 64 * wave + c;
-    const uint32_t k1 = ks[0];
-    uint32_t rk[NR + 1];
-#pragma unroll
-    for (int r = 2; r <= NR; ++r) rk[r] = ks[4 + 4 * r];
+__device__ __forceinline__ uint32_t quad_load(const uint8_t *in, uint64_t at, uint64_t len, uint32_t have)
+{
+    g_cu8 *p = len >= 4 ? (g_cu8 *)in + (have == 4 ? at : 0) : (g_cu8 *)&g_dummy;
+    return __builtin_nontemporal_load((g_cu32 *)p);
+}
+
+__device__ __forceinline__ uint32_t quad_load_rest(const uint8_t *in, uint64_t at, uint32_t have, uint32_t d)
+{
     if (have < 4) {
+        g_cu8 *p = (g_cu8 *)in + at;
         d = 0;
 #pragma unroll
         for (uint32_t i = 0; i < 3; ++i)
             if (i < have)
-                d |= static_cast<uint32_t>(src[i]) << (8 * i);
+                d |= static_cast<uint32_t>(p[i]) << (8 * i);
     }
+    return d;
+}
 
+__device__ __forceinline__ void quad_store(uint8_t *out, uint64_t at, uint32_t have, uint32_t d)
+{
+    g_u8 *p = (g_u8 *)out + at;
+    if (have == 4) {
+        __builtin_nontemporal_store(d, (g_u32 *)p);
+    } else {
+#pragma unroll
+        for (uint32_t i = 0; i < 3; ++i)
+            if (i < have)
+                p[i] = static_cast<uint8_t>(d >> (8 * i));
+    }
+}
+
+// Word c of the keystream block of counter ctr.  ks: the key material (CtrKeys) from word c on.
+template <int NR>
+__device__ __forceinline__ uint32_t quad_keystream(const uint32_t *lds, const uint32_t *ks, uint32_t c, uint32_t ctr,
+                                                   uint32_t x0)
+{
+    const uint32_t k1 = ks[0];
+    uint32_t rk[NR + 1];
+#pragma unroll
+    for (int r = 2; r <= NR; ++r) rk[r] = ks[4 + 4 * r];
     // Rounds 0 and 1: column c takes byte 3 - c of the counter column.
-    const uint32_t ctr = ctr0 + static_cast<uint32_t>(blk);
     const uint32_t x = vperm(ctr, ctr, 0x00010203u) ^ x0;    // big-endian counter
     uint32_t s = k1 ^ lds[256 * (3 - c) + __builtin_amdgcn_ubfe(x, 24 - 8 * c, 8)];
 #pragma unroll
@@ -91,16 +108,82 @@ __global__ __launch_bounds__(kQuadWG) void ctr_quad_kernel(const uint8_t *in, ui
     const uint32_t s1 = quad<0x39>(s), s2 = quad<0x4e>(s), s3 = quad<0x93>(s);
     const uint32_t lo = vperm(lds[(s1 >> 8) & 255u], lds[512 + (s & 255u)], 0x0c0c0500u);
     const uint32_t hi = vperm(lds[512 + (s3 >> 24)], lds[(s2 >> 16) & 255u], 0x07020c0cu);
-    d ^= xor3(lo, hi, rk[NR]);
+    return xor3(lo, hi, rk[NR]);
+}
 
-    g_u8 *dst = (g_u8 *)out + at;
-    if (have == 4) {
-        __builtin_nontemporal_store(d, (g_u32 *)dst);
-    } else {
+template <int NR>
+__global__ __launch_bounds__(kQuadWG) void ctr_quad_kernel(const uint8_t *in, uint8_t *out, uint64_t len, uint32_t ctr0,
+                                                           uint32_t x0, const CtrKeys keys)
+{
+    __shared__ uint32_t lds[4 * 256];   // table t at word 256 t
+    __shared__ uint32_t lkeys[kQuadWG];
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane & 3;
+    const u32x4 t0 = reinterpret_cast<const u32x4 *>(c_round.t[0])[lane];
+    const uint32_t kw = key_word(lane);
+    __builtin_amdgcn_sched_barrier(0);
+    quad_fill(lds, t0, wave, lane);
+    lkeys[threadIdx.x] = kw;            // each wave for itself
+    __builtin_amdgcn_sched_barrier(0);
+
+    const uint64_t blk = static_cast<uint64_t>(blockIdx.x) * kBlocks + (threadIdx.x >> 2);
+    const uint64_t at = 16 * blk + 4 * c;
+    const uint32_t have = quad_have(at, len);
+    uint32_t d = quad_load(in, at, len, have);
+    __syncthreads();
+    d = quad_load_rest(in, at, have, d);
+    d ^= quad_keystream<NR>(lds, lkeys + 64 * wave + c, c, ctr0 + static_cast<uint32_t>(blk), x0);
+    quad_store(out, at, have, d);
+}
+
+// A few small requests whose records travel in the kernel argument block
+// (SmallBatchArgs, tile_blocks = kBlocks): workgroup t takes tile t.
+__global__ __launch_bounds__(kQuadWG) void ctr_quad_batch_kernel(const SmallBatchArgs args)
+{
+    __shared__ uint32_t lds[4 * 256];
+    __shared__ uint32_t lkeys[kQuadWG];
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane & 3, t = blockIdx.x;
+    const u32x4 t0 = reinterpret_cast<const u32x4 *>(c_round.t[0])[lane];
+    const uint32_t n = args.n;
+    // Last request whose first tile is <= t (skips empty requests).
+    uint32_t r = 0;
 #pragma unroll
-        for (uint32_t i = 0; i < 3; ++i)
-            if (i < have)
-                dst[i] = static_cast<uint8_t>(d >> (8 * i));
+    for (uint32_t i = 1; i < kSmallBatch; ++i)
+        if (i < n && args.r[i].tile0 <= t)
+            r = i;
+    const SmallRec &R = args.r[r];
+    uint32_t *resident = reinterpret_cast<uint32_t *>(args.resident);
+    uint32_t kw = 0;
+    if (lane < 4)
+        kw = R.k1[lane];
+    else if (R.key & kKeyResident)
+        kw = resident[64u * (R.key & ~kKeyResident) + lane - 4];
+    else
+        kw = R.rk[lane - 4];
+    const uint8_t *in = reinterpret_cast<const uint8_t *>(R.in);
+    const uint64_t blk = static_cast<uint64_t>(t - R.tile0) * kBlocks + (threadIdx.x >> 2);
+    const uint64_t at = 16 * blk + 4 * c;
+    const bool any = t < args.total_tiles;     // no tile at all: a launch for its installs
+    const uint64_t len = any ? R.len : 0;
+    const uint32_t have = quad_have(at, len);
+    const uint32_t ctr = R.ctr0 + static_cast<uint32_t>(blk), x0 = R.x0, nr = R.nr;
+    uint8_t *out = reinterpret_cast<uint8_t *>(R.out);
+    quad_fill(lds, t0, wave, lane);
+    lkeys[threadIdx.x] = kw;
+    uint32_t d = quad_load(in, at, len, have);
+    __syncthreads();
+    if (any) {
+        d = quad_load_rest(in, at, have, d);
+        const uint32_t *ks = lkeys + 64 * wave + c;
+        d ^= nr == 10 ? quad_keystream<10>(lds, ks, c, ctr, x0) : quad_keystream<14>(lds, ks, c, ctr, x0);
+        quad_store(out, at, have, d);
+    }
+    // No wave of this launch reads a slot that it installs.
+    if (t == 0) {
+        for (uint32_t j = threadIdx.x; j < 64u * n; j += kQuadWG) {
+            const uint32_t i = j >> 6, w = j & 63u;
+            if (args.r[i].install != kNoInstall && w < 60u)
+                resident[64u * args.r[i].install + w] = args.r[i].rk[w];
+        }
     }
 }
 
@@ -135,6 +218,16 @@ int launch_ctr_quad(const CtrArgs &a, int nr, hipStream_t st)
         launch_quad<14>(a, st);
     else
         return AES_EINVAL;
+    return launch_status();
+}
+
+int launch_ctr_quad_batch(const SmallBatchArgs &args, hipStream_t st)
+{
+    if (args.n > kSmallBatch || args.tile_blocks != kQuadTileBlocks || args.total_tiles > 0x7fffffffu)
+        return AES_EINVAL;
+    (void)hipGetLastError();   // not ours: left by earlier calls
+    const dim3 grid(args.total_tiles ? args.total_tiles : 1);
+    hipLaunchKernelGGL(ctr_quad_batch_kernel, grid, dim3(kQuadWG), 0, st, args);
     return launch_status();
 }
 
