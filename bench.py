@@ -300,7 +300,7 @@ def measured_traffic(bits, size, variant):
 # 8 MiB, table fill and per-wave setup included: rocprofv3 SQ_INSTS_VALU x 64
 # / blocks (two-table layout, 512-thread workgroups, two per CU, each wave
 # computing its first chunk's group constants).
-VALU_PER_BLOCK_8MIB = {128: 329.5, 256: 449.5}
+VALU_PER_BLOCK_8MIB = {128: 329.0, 256: 449.0}
 # VALU lane operations per block of the kernels without LDS tables: the
 # bitsliced and the vector-permute kernels (rocprofv3 SQ_INSTS_VALU at 256 MiB).
 VALU_PER_BLOCK_BS = {128: 678, 256: 934}
@@ -373,7 +373,9 @@ def tune_source(A, variant, bits, size, shape=None):
     """Where a launch shape comes from: the library reads the autotuner's
     cache (AESCTR_TUNE_CACHE, else tune_cache.json beside libaesctr.so) and
     takes the entry of the same variant and key size whose size_log2 is
-    floor(log2(size)); without one it keeps its built-in rule.  Reports that
+    floor(log2(size)), the T-table kernel's only if its grid takes the message
+    in as many chunks as the size it was tuned at; without one it keeps its
+    built-in rule.  Reports that
     entry, the cache's timestamp, and whether the shape in use is the entry's
     (variant 10 is the batch kernel's tiling)."""
     path = os.environ.get("AESCTR_TUNE_CACHE") or os.path.join(os.path.dirname(A._native.LIB_PATH),

@@ -160,10 +160,6 @@ int build_graph(BatchCtx *c, int s, int grid, int bpl)
 
 }  // namespace
 
-// Completes a staged table at buf: n descriptors, header.n_keys inline keys
-// and header.n_install installs written.  Assigns first tiles and fills the
-// rest of the header.  Returns the bytes to upload, or 0 if the tile count
-// would overflow.
 uint32_t batch_own_tiles(uint64_t tiles, int grid)
 {
     // A claim from the header's counter is a device-wide atomic on one word:
@@ -175,6 +171,10 @@ uint32_t batch_own_tiles(uint64_t tiles, int grid)
     return static_cast<uint32_t>(per_wg >= 64 ? per_wg - per_wg / 12 : per_wg);
 }
 
+// Completes a staged table at buf: n descriptors, header.n_keys inline keys
+// and header.n_install installs written.  Assigns first tiles and fills the
+// rest of the header.  Returns the bytes to upload, or 0 if the tile count
+// would overflow.
 size_t finish_stage(uint8_t *buf, size_t n, uint32_t tile_blocks, int grid)
 {
     BatchHeader *h = reinterpret_cast<BatchHeader *>(buf);
@@ -202,6 +202,7 @@ namespace {
 // Records per part of the host's parallel record building.
 constexpr size_t kRecordGrain = 256;
 
+// Workgroups that a request of len bytes takes at four lanes per block.
 uint64_t quad_tiles(uint64_t len)
 {
     return len / (16 * kQuadTileBlocks) + (len % (16 * kQuadTileBlocks) != 0);
