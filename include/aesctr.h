@@ -212,8 +212,8 @@ int aes_ctr_crypt_batch(const aes_ctr_desc_t *desc, size_t n, void *stream);
  * uses the graph; batches of at most 8 requests use neither: their kernel
  * has 256-thread workgroups, a wave per tile up to twice `grid` workgroups,
  * and takes tile_bytes and blocks_per_lane from cfg like the table kernel, or,
- * where twice `grid` workgroups hold it all that way, runs 64 blocks of a
- * request per workgroup, four lanes per block. */
+ * where that holds it all, runs with four lanes per block (workgroups of 64
+ * blocks, up to twice `grid` of them) or two (of 256 blocks, up to `grid`). */
 typedef struct {
     int32_t tile_bytes;
     int32_t wg_size;

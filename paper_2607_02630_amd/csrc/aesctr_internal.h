@@ -244,10 +244,11 @@ static_assert(sizeof(SmallBatchArgs) <= 4096, "kernel arguments are limited to 4
 // grid: workgroups of the argument-path kernel's own size (256 threads).
 int launch_ctr_batch_small(const SmallBatchArgs &args, int grid, int bpl, hipStream_t st);
 
-// Four lanes per block (ctr_quad.hip), a workgroup per tile of this many blocks
-// from a request's start.
-constexpr uint32_t kQuadTileBlocks = 64;
+// Four or two lanes per block (ctr_quad.hip, ctr_pair.hip), a workgroup per tile
+// of this many blocks from a request's start; pairs need at least one tile.
+constexpr uint32_t kQuadTileBlocks = 64, kPairTileBlocks = 256;
 int launch_ctr_quad_batch(const SmallBatchArgs &args, hipStream_t st);
+int launch_ctr_pair_batch(const SmallBatchArgs &args, hipStream_t st);
 
 // One request as the host keeps it before staging: its descriptor (key field
 // not yet assigned) and its round keys.

@@ -202,32 +202,39 @@ namespace {
 // Records per part of the host's parallel record building.
 constexpr size_t kRecordGrain = 256;
 
-// Workgroups that a request of len bytes takes at four lanes per block.
-uint64_t quad_tiles(uint64_t len)
+// Tiles of tile_blocks blocks from a request's start.
+uint64_t plain_tiles(uint64_t len, uint32_t tile_blocks)
 {
-    return len / (16 * kQuadTileBlocks) + (len % (16 * kQuadTileBlocks) != 0);
+    return len / (16 * tile_blocks) + (len % (16 * tile_blocks) != 0);
 }
 
 // A batch of at most kSmallBatch requests goes in the kernel's argument block
-// (no staging slot, no upload), to one of two kernels whose grid it sizes.
-// Where the requests are few enough for two workgroups per CU of the table
-// kernel's grid (which is at most one per CU) at four lanes per block, they run
-// so (ctr_quad.hip); the limit is the single message's (quad_shape).  Else a wave
-// per tile in workgroups of four waves, at most two workgroups per CU too, the
-// waves looping over further tiles.  us per call back to back, and for one call
-// up to its end, in brackets those of the other kernel: one request of 64 KiB 4.6
-// (7.8) and 15.2 (19.5); one of 512 KiB 4.6 (8.0) and 16.0 (19.6); 8 of 100 bytes
-// 4.8 (8.7) and 15.2 (19.3); 8 of 64 KiB 4.8 (9.6) and 16.0 (21.4); the same 8 in
-// pinned host memory, one call, 30.2 (33.4).
+// (no staging slot, no upload), to one of three kernels whose grid it sizes.
+// Where four lanes per block make at most two workgroups per CU of the table
+// kernel's grid (which is at most one per CU), the requests run so
+// (ctr_quad.hip); else with two lanes per block where that makes at most one
+// (ctr_pair.hip); the limits are the single message's (quad_shape, pair_shape).
+// Else a wave per tile in workgroups of four waves, at most two workgroups per CU
+// too, the waves looping over further tiles.  us per call back to back, and for
+// one call up to its end, in brackets those of the last kernel.  Quads: one
+// request of 64 KiB 4.6 (7.8) and 15.2 (19.5); one of 512 KiB 4.6 (8.0) and 16.0
+// (19.6); 8 of 100 bytes 4.8 (8.7) and 15.2 (19.3); 8 of 64 KiB 4.8 (9.6) and 16.0
+// (21.4), in pinned host memory 30.2 (33.4) for one call.  Pairs: one request of 1
+// MiB 4.8 (8.1) and 17.0 (20.2); 8 of 128 KiB 4.8 (9.6) and 16.9 (21.9), in pinned
+// host memory 47.5 (49.7).
 // Returns AES_OK, AES_ERANGE or AES_EDEVICE.
 int launch_small(hipStream_t st, const LaunchSpec &spec, uint32_t tile_blocks, int grid, int bpl)
 {
     SmallBatchArgs args{};
     const uint64_t cap = 2 * static_cast<uint64_t>(grid);
-    uint64_t quads = 0;
-    for (size_t i = 0; i < spec.n; ++i)
-        quads += quad_tiles(spec.descs[i].len);
-    const bool quad = quads <= cap;
+    uint64_t quads = 0, pairs = 0;
+    for (size_t i = 0; i < spec.n; ++i) {
+        quads += plain_tiles(spec.descs[i].len, kQuadTileBlocks);
+        pairs += plain_tiles(spec.descs[i].len, kPairTileBlocks);
+    }
+    const bool quad = quads <= cap, pair = !quad && pairs <= static_cast<uint64_t>(grid);
+    if (quad || pair)
+        tile_blocks = quad ? kQuadTileBlocks : kPairTileBlocks;
     uint64_t tiles = 0;
     for (size_t i = 0; i < spec.n; ++i) {
         const BatchDesc &d = spec.descs[i];
@@ -248,7 +255,7 @@ int launch_small(hipStream_t st, const LaunchSpec &spec, uint32_t tile_blocks, i
                     r.install = spec.installs[j].slot;
         }
         r.tile0 = static_cast<uint32_t>(tiles);
-        tiles += quad ? quad_tiles(d.len) : request_tiles(d.len, d.ctr0, tile_blocks);
+        tiles += quad || pair ? plain_tiles(d.len, tile_blocks) : request_tiles(d.len, d.ctr0, tile_blocks);
         if (tiles > 0x7fffffffu)
             return AES_ERANGE;
     }
@@ -260,10 +267,12 @@ int launch_small(hipStream_t st, const LaunchSpec &spec, uint32_t tile_blocks, i
                 args.r[i].install = kNoInstall;
     args.n = static_cast<uint32_t>(spec.n);
     args.total_tiles = static_cast<uint32_t>(tiles);
-    args.tile_blocks = quad ? kQuadTileBlocks : tile_blocks;
+    args.tile_blocks = tile_blocks;
     args.resident = spec.resident;
     if (quad)
         return launch_ctr_quad_batch(args, st);
+    if (pair)
+        return launch_ctr_pair_batch(args, st);
     const uint64_t want = (tiles + 3) / 4;
     const int small_grid = static_cast<int>(std::max<uint64_t>(1, std::min(want, cap)));
     return launch_ctr_batch_small(args, small_grid, bpl, st);

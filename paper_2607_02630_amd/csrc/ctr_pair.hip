@@ -15,6 +15,8 @@
 // waited for both: 1 MiB 3.06 us; with the message behind the fill, 2.86).
 // Measured per launch in a replayed graph, against one lane per block: AES-128,
 // 640 KiB 2.69 us (3.28), 1 MiB 2.79 (3.26); AES-256, 3.04 (3.74), 3.12 (3.81).
+// Batches of a few requests of this size in all take the same path
+// (ctr_pair_batch_kernel; figures at launch_small in batch.cpp).
 #include "ttable_device.h"
 
 namespace aesctr {
@@ -22,6 +24,7 @@ namespace {
 
 constexpr int kPairWG = 512;
 constexpr uint32_t kBlocks = kPairWG / 2;   // per workgroup
+static_assert(kBlocks == kPairTileBlocks, "the tile of a small batch");
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(1)));
@@ -51,6 +54,90 @@ __device__ __forceinline__ uint32_t last_column(const TTable<kLayout2x32> &tt, u
                 vperm(tt.raw<1, 3>(s3), tt.raw<0, 2>(s2), 0x07020c0cu), k);
 }
 
+// Whether this lane has all of its half block at byte `at` of a message of len, or the
+// bytes it has of it; the loads of the lanes without all go to valid memory.  (One
+// yes or no for load and store: a byte count tested at both ends becomes a chain
+// of branches at the store, 1 MiB 2.82 us instead of 2.76.)
+__device__ __forceinline__ bool pair_whole(uint64_t at, uint64_t len) { return at + 8 <= len; }
+
+__device__ __forceinline__ uint32_t pair_rest(uint64_t at, uint64_t len)
+{
+    return at < len ? static_cast<uint32_t>(len - at) : 0;
+}
+
+__device__ __forceinline__ u32x2 pair_load(const uint8_t *in, uint64_t at, uint64_t len, bool whole)
+{
+    g_cu8 *p = len >= 8 ? (g_cu8 *)in + (whole ? at : 0) : (g_cu8 *)&g_dummy;
+    return __builtin_nontemporal_load((g_cu32x2 *)p);
+}
+
+__device__ __forceinline__ u32x2 pair_load_rest(const uint8_t *in, uint64_t at, uint64_t len, bool whole, u32x2 d)
+{
+    if (!whole) {
+        const uint32_t have = pair_rest(at, len);
+        g_cu8 *p = (g_cu8 *)in + at;
+        d = u32x2{0, 0};
+#pragma unroll
+        for (uint32_t i = 0; i < 7; ++i)
+            if (i < have)
+                d[i >> 2] |= static_cast<uint32_t>(p[i]) << (8 * (i & 3));
+    }
+    return d;
+}
+
+__device__ __forceinline__ void pair_store(uint8_t *out, uint64_t at, uint64_t len, bool whole, u32x2 d)
+{
+    g_u8 *p = (g_u8 *)out + at;
+    if (whole) {
+        __builtin_nontemporal_store((u32x2_any)d, (g_u32x2 *)p);
+    } else {
+        const uint32_t have = pair_rest(at, len);
+#pragma unroll
+        for (uint32_t i = 0; i < 7; ++i)
+            if (i < have)
+                p[i] = static_cast<uint8_t>(d[i >> 2] >> (8 * (i & 3)));
+    }
+}
+
+// Key word `lane` as it goes to LDS: those of the inner rounds rotated for the
+// two-table fold.
+__device__ __forceinline__ uint32_t pair_key(uint32_t kw, uint32_t lane, uint32_t nr)
+{
+    return lane >= 4 && lane < 4 + 4 * nr ? rotr8(kw) : kw;
+}
+
+// The lane's keys of rounds 1 (k1) .. NR from the key material (pair_key) from word
+// 2c on.  Apart from the rounds because they go ahead of pair_load_rest: behind
+// its branch, every launch of 1 MiB takes 2.85 us instead of 2.82.
+template <int NR>
+__device__ __forceinline__ void pair_keys(const u32x2 *ks, u32x2 (&k)[NR + 1])
+{
+    k[1] = ks[0];
+#pragma unroll
+    for (int r = 2; r <= NR; ++r) k[r] = ks[2 + 2 * r];
+}
+
+// Words 2c and 2c + 1 of the keystream block of counter ctr.
+template <int NR>
+__device__ __forceinline__ u32x2 pair_keystream(const TTable<kLayout2x32> &tt, const u32x2 (&k)[NR + 1], uint32_t c,
+                                                uint32_t ctr, uint32_t x0)
+{
+    // Rounds 0 and 1: column j takes byte 3 - j of the counter column, by table 3 - j.
+    const uint32_t x = vperm(ctr, ctr, 0x00010203u) ^ x0;    // big-endian counter
+    const uint32_t lb = tt.lb0 + (c ? 0 : 128);              // T2 for columns 0 and 1
+    uint32_t a = k[1][0] ^ rotl8(lds_at(tt.lds, (__builtin_amdgcn_ubfe(x, c ? 8 : 24, 8) << 8) + lb));
+    uint32_t b = k[1][1] ^ lds_at(tt.lds, (__builtin_amdgcn_ubfe(x, c ? 0 : 16, 8) << 8) + lb);
+#pragma unroll
+    for (int r = 2; r < NR; ++r) {
+        const uint32_t oa = other(a), ob = other(b);
+        const uint32_t na = column(tt, a, b, oa, ob, k[r][0]);
+        b = column(tt, b, oa, ob, a, k[r][1]);
+        a = na;
+    }
+    const uint32_t oa = other(a), ob = other(b);
+    return u32x2{last_column(tt, a, b, oa, ob, k[NR][0]), last_column(tt, b, oa, ob, a, k[NR][1])};
+}
+
 template <int NR>
 __global__ __launch_bounds__(kPairWG) void ctr_pair_kernel(const uint8_t *in, uint8_t *out, uint64_t len, uint32_t ctr0,
                                                            uint32_t x0, const CtrKeys keys)
@@ -61,61 +148,79 @@ __global__ __launch_bounds__(kPairWG) void ctr_pair_kernel(const uint8_t *in, ui
     const uint32_t kw = key_word(lane);
     uint32_t tv[kFillStores / kPairWG];
     fill_read<kLayout2x32, kPairWG>(tv);
-
-    // This lane's half of its block; of the last, partial block the bytes there are.
     const uint64_t blk = static_cast<uint64_t>(blockIdx.x) * kBlocks + (threadIdx.x >> 1);
     const uint64_t at = 16 * blk + 8 * c;
-    const uint32_t have = at + 8 <= len ? 8 : at < len ? static_cast<uint32_t>(len - at) : 0;
-    g_cu8 *src = (g_cu8 *)in + at;
-    g_cu8 *whole = len >= 8 ? (g_cu8 *)in + (have == 8 ? at : 0) : (g_cu8 *)&g_dummy;
-    u32x2 d = __builtin_nontemporal_load((g_cu32x2 *)whole);
+    const bool whole = pair_whole(at, len);
+    u32x2 d = pair_load(in, at, len, whole);
     __builtin_amdgcn_sched_barrier(0);
 
-    // Each wave keeps the keys for itself, those of the inner rounds rotated for
-    // the two-table fold.
     fill_write<kLayout2x32, kPairWG>(lds, tv);
-    reinterpret_cast<uint32_t *>(lkeys)[threadIdx.x] = lane >= 4 && lane < 4 + 4 * NR ? rotr8(kw) : kw;
+    reinterpret_cast<uint32_t *>(lkeys)[threadIdx.x] = pair_key(kw, lane, NR);   // each wave for itself
     __syncthreads();
-
-    const u32x2 *ks = lkeys + 32 * wave + c;
-    const u32x2 k1 = ks[0];
-    u32x2 rk[NR + 1];
-#pragma unroll
-    for (int r = 2; r <= NR; ++r) rk[r] = ks[2 + 2 * r];
-    if (have < 8) {
-        d = u32x2{0, 0};
-#pragma unroll
-        for (uint32_t i = 0; i < 7; ++i)
-            if (i < have)
-                d[i >> 2] |= static_cast<uint32_t>(src[i]) << (8 * (i & 3));
-    }
-
-    // Rounds 0 and 1: column j takes byte 3 - j of the counter column, by table 3 - j.
+    u32x2 k[NR + 1];
+    pair_keys<NR>(lkeys + 32 * wave + c, k);
+    d = pair_load_rest(in, at, len, whole, d);
     const TTable<kLayout2x32> tt{reinterpret_cast<const char *>(lds), 4 * (lane & 31), 0};
-    const uint32_t ctr = ctr0 + static_cast<uint32_t>(blk);
-    const uint32_t x = vperm(ctr, ctr, 0x00010203u) ^ x0;    // big-endian counter
-    const uint32_t lb = tt.lb0 + (c ? 0 : 128);              // T2 for columns 0 and 1
-    uint32_t a = k1[0] ^ rotl8(lds_at(tt.lds, (__builtin_amdgcn_ubfe(x, c ? 8 : 24, 8) << 8) + lb));
-    uint32_t b = k1[1] ^ lds_at(tt.lds, (__builtin_amdgcn_ubfe(x, c ? 0 : 16, 8) << 8) + lb);
-#pragma unroll
-    for (int r = 2; r < NR; ++r) {
-        const uint32_t oa = other(a), ob = other(b);
-        const uint32_t na = column(tt, a, b, oa, ob, rk[r][0]);
-        b = column(tt, b, oa, ob, a, rk[r][1]);
-        a = na;
-    }
-    const uint32_t oa = other(a), ob = other(b);
-    d[0] ^= last_column(tt, a, b, oa, ob, rk[NR][0]);
-    d[1] ^= last_column(tt, b, oa, ob, a, rk[NR][1]);
+    d ^= pair_keystream<NR>(tt, k, c, ctr0 + static_cast<uint32_t>(blk), x0);
+    pair_store(out, at, len, whole, d);
+}
 
-    g_u8 *dst = (g_u8 *)out + at;
-    if (have == 8) {
-        __builtin_nontemporal_store((u32x2_any)d, (g_u32x2 *)dst);
-    } else {
+// A few requests whose records travel in the kernel argument block
+// (SmallBatchArgs, tile_blocks = kBlocks): workgroup t takes tile t.
+__global__ __launch_bounds__(kPairWG) void ctr_pair_batch_kernel(const SmallBatchArgs args)
+{
+    __shared__ uint32_t lds[layout_lds_words(kLayout2x32)];
+    __shared__ u32x2 lkeys[kPairWG / 2];
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane & 1, t = blockIdx.x;
+    uint32_t tv[kFillStores / kPairWG];
+    fill_read<kLayout2x32, kPairWG>(tv);
+    const uint32_t n = args.n;
+    // Last request whose first tile is <= t (skips empty requests).
+    uint32_t r = 0;
 #pragma unroll
-        for (uint32_t i = 0; i < 7; ++i)
-            if (i < have)
-                dst[i] = static_cast<uint8_t>(d[i >> 2] >> (8 * (i & 3)));
+    for (uint32_t i = 1; i < kSmallBatch; ++i)
+        if (i < n && args.r[i].tile0 <= t)
+            r = i;
+    const SmallRec &R = args.r[r];
+    uint32_t *resident = reinterpret_cast<uint32_t *>(args.resident);
+    uint32_t kw = 0;
+    if (lane < 4)
+        kw = R.k1[lane];
+    else if (R.key & kKeyResident)
+        kw = resident[64u * (R.key & ~kKeyResident) + lane - 4];
+    else
+        kw = R.rk[lane - 4];
+    const uint8_t *in = reinterpret_cast<const uint8_t *>(R.in);
+    uint8_t *out = reinterpret_cast<uint8_t *>(R.out);
+    const uint64_t len = R.len;
+    const uint64_t blk = static_cast<uint64_t>(t - R.tile0) * kBlocks + (threadIdx.x >> 1);
+    const uint64_t at = 16 * blk + 8 * c;
+    const bool whole = pair_whole(at, len);
+    const uint32_t ctr = R.ctr0 + static_cast<uint32_t>(blk), x0 = R.x0, nr = R.nr;
+    u32x2 d = pair_load(in, at, len, whole);
+    fill_write<kLayout2x32, kPairWG>(lds, tv);
+    reinterpret_cast<uint32_t *>(lkeys)[threadIdx.x] = pair_key(kw, lane, nr);
+    __syncthreads();
+    d = pair_load_rest(in, at, len, whole, d);
+    const TTable<kLayout2x32> tt{reinterpret_cast<const char *>(lds), 4 * (lane & 31), 0};
+    const u32x2 *ks = lkeys + 32 * wave + c;
+    if (nr == 10) {
+        u32x2 k[11];
+        pair_keys<10>(ks, k);
+        d ^= pair_keystream<10>(tt, k, c, ctr, x0);
+    } else {
+        u32x2 k[15];
+        pair_keys<14>(ks, k);
+        d ^= pair_keystream<14>(tt, k, c, ctr, x0);
+    }
+    pair_store(out, at, len, whole, d);
+    // No wave of this launch reads a slot that it installs.
+    if (t == 0) {
+        for (uint32_t j = threadIdx.x; j < 64u * n; j += kPairWG) {
+            const uint32_t i = j >> 6, w = j & 63u;
+            if (args.r[i].install != kNoInstall && w < 60u)
+                resident[64u * args.r[i].install + w] = args.r[i].rk[w];
+        }
     }
 }
 
@@ -151,6 +256,16 @@ int launch_ctr_pair(const CtrArgs &a, int nr, hipStream_t st)
         launch_pair<14>(a, st);
     else
         return AES_EINVAL;
+    return launch_status();
+}
+
+int launch_ctr_pair_batch(const SmallBatchArgs &args, hipStream_t st)
+{
+    if (args.n > kSmallBatch || args.tile_blocks != kPairTileBlocks || args.total_tiles == 0 ||
+        args.total_tiles > 0x7fffffffu)
+        return AES_EINVAL;
+    (void)hipGetLastError();   // not ours: left by earlier calls
+    hipLaunchKernelGGL(ctr_pair_batch_kernel, dim3(args.total_tiles), dim3(kPairWG), 0, st, args);
     return launch_status();
 }
 

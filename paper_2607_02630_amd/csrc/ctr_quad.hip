@@ -47,22 +47,25 @@ __device__ __forceinline__ void quad_fill(uint32_t *lds, u32x4 t0, uint32_t wave
     *reinterpret_cast<u32x4 *>(&lds[256 * wave + 4 * lane]) = v;
 }
 
-// Bytes that this lane has of its word at byte `at` of a message of len, and the
-// word if it has all of it; the loads of the other lanes go to valid memory.
-__device__ __forceinline__ uint32_t quad_have(uint64_t at, uint64_t len)
+// Whether this lane has all of its word at byte `at` of a message of len, or the
+// bytes it has of it; the loads of the lanes without all go to valid memory.
+__device__ __forceinline__ bool quad_whole(uint64_t at, uint64_t len) { return at + 4 <= len; }
+
+__device__ __forceinline__ uint32_t quad_rest(uint64_t at, uint64_t len)
 {
-    return at + 4 <= len ? 4 : at < len ? static_cast<uint32_t>(len - at) : 0;
+    return at < len ? static_cast<uint32_t>(len - at) : 0;
 }
 
-__device__ __forceinline__ uint32_t quad_load(const uint8_t *in, uint64_t at, uint64_t len, uint32_t have)
+__device__ __forceinline__ uint32_t quad_load(const uint8_t *in, uint64_t at, uint64_t len, bool whole)
 {
-    g_cu8 *p = len >= 4 ? (g_cu8 *)in + (have == 4 ? at : 0) : (g_cu8 *)&g_dummy;
+    g_cu8 *p = len >= 4 ? (g_cu8 *)in + (whole ? at : 0) : (g_cu8 *)&g_dummy;
     return __builtin_nontemporal_load((g_cu32 *)p);
 }
 
-__device__ __forceinline__ uint32_t quad_load_rest(const uint8_t *in, uint64_t at, uint32_t have, uint32_t d)
+__device__ __forceinline__ uint32_t quad_load_rest(const uint8_t *in, uint64_t at, uint64_t len, bool whole, uint32_t d)
 {
-    if (have < 4) {
+    if (!whole) {
+        const uint32_t have = quad_rest(at, len);
         g_cu8 *p = (g_cu8 *)in + at;
         d = 0;
 #pragma unroll
@@ -73,12 +76,13 @@ __device__ __forceinline__ uint32_t quad_load_rest(const uint8_t *in, uint64_t a
     return d;
 }
 
-__device__ __forceinline__ void quad_store(uint8_t *out, uint64_t at, uint32_t have, uint32_t d)
+__device__ __forceinline__ void quad_store(uint8_t *out, uint64_t at, uint64_t len, bool whole, uint32_t d)
 {
     g_u8 *p = (g_u8 *)out + at;
-    if (have == 4) {
+    if (whole) {
         __builtin_nontemporal_store(d, (g_u32 *)p);
     } else {
+        const uint32_t have = quad_rest(at, len);
 #pragma unroll
         for (uint32_t i = 0; i < 3; ++i)
             if (i < have)
@@ -86,29 +90,34 @@ __device__ __forceinline__ void quad_store(uint8_t *out, uint64_t at, uint32_t h
     }
 }
 
-// Word c of the keystream block of counter ctr.  ks: the key material (CtrKeys) from word c on.
+// The lane's keys of rounds 1 (k1) .. NR from the key material (CtrKeys) from word c on.
 template <int NR>
-__device__ __forceinline__ uint32_t quad_keystream(const uint32_t *lds, const uint32_t *ks, uint32_t c, uint32_t ctr,
-                                                   uint32_t x0)
+__device__ __forceinline__ void quad_keys(const uint32_t *ks, uint32_t (&k)[NR + 1])
 {
-    const uint32_t k1 = ks[0];
-    uint32_t rk[NR + 1];
+    k[1] = ks[0];
 #pragma unroll
-    for (int r = 2; r <= NR; ++r) rk[r] = ks[4 + 4 * r];
+    for (int r = 2; r <= NR; ++r) k[r] = ks[4 + 4 * r];
+}
+
+// Word c of the keystream block of counter ctr.
+template <int NR>
+__device__ __forceinline__ uint32_t quad_keystream(const uint32_t *lds, const uint32_t (&k)[NR + 1], uint32_t c,
+                                                   uint32_t ctr, uint32_t x0)
+{
     // Rounds 0 and 1: column c takes byte 3 - c of the counter column.
     const uint32_t x = vperm(ctr, ctr, 0x00010203u) ^ x0;    // big-endian counter
-    uint32_t s = k1 ^ lds[256 * (3 - c) + __builtin_amdgcn_ubfe(x, 24 - 8 * c, 8)];
+    uint32_t s = k[1] ^ lds[256 * (3 - c) + __builtin_amdgcn_ubfe(x, 24 - 8 * c, 8)];
 #pragma unroll
     for (int r = 2; r < NR; ++r) {
         const uint32_t s1 = quad<0x39>(s), s2 = quad<0x4e>(s), s3 = quad<0x93>(s);   // columns c + 1, 2, 3
         s = xor3(xor3(lds[s & 255u], lds[256 + ((s1 >> 8) & 255u)], lds[512 + ((s2 >> 16) & 255u)]),
-                 lds[768 + (s3 >> 24)], rk[r]);
+                 lds[768 + (s3 >> 24)], k[r]);
     }
     // The last round's S bytes: T0 holds S in bytes 1 and 2, T2 in bytes 0 and 3.
     const uint32_t s1 = quad<0x39>(s), s2 = quad<0x4e>(s), s3 = quad<0x93>(s);
     const uint32_t lo = vperm(lds[(s1 >> 8) & 255u], lds[512 + (s & 255u)], 0x0c0c0500u);
     const uint32_t hi = vperm(lds[512 + (s3 >> 24)], lds[(s2 >> 16) & 255u], 0x07020c0cu);
-    return xor3(lo, hi, rk[NR]);
+    return xor3(lo, hi, k[NR]);
 }
 
 template <int NR>
@@ -127,12 +136,14 @@ __global__ __launch_bounds__(kQuadWG) void ctr_quad_kernel(const uint8_t *in, ui
 
     const uint64_t blk = static_cast<uint64_t>(blockIdx.x) * kBlocks + (threadIdx.x >> 2);
     const uint64_t at = 16 * blk + 4 * c;
-    const uint32_t have = quad_have(at, len);
-    uint32_t d = quad_load(in, at, len, have);
+    const bool whole = quad_whole(at, len);
+    uint32_t d = quad_load(in, at, len, whole);
     __syncthreads();
-    d = quad_load_rest(in, at, have, d);
-    d ^= quad_keystream<NR>(lds, lkeys + 64 * wave + c, c, ctr0 + static_cast<uint32_t>(blk), x0);
-    quad_store(out, at, have, d);
+    uint32_t k[NR + 1];
+    quad_keys<NR>(lkeys + 64 * wave + c, k);
+    d = quad_load_rest(in, at, len, whole, d);
+    d ^= quad_keystream<NR>(lds, k, c, ctr0 + static_cast<uint32_t>(blk), x0);
+    quad_store(out, at, len, whole, d);
 }
 
 // A few small requests whose records travel in the kernel argument block
@@ -164,18 +175,26 @@ __global__ __launch_bounds__(kQuadWG) void ctr_quad_batch_kernel(const SmallBatc
     const uint64_t at = 16 * blk + 4 * c;
     const bool any = t < args.total_tiles;     // no tile at all: a launch for its installs
     const uint64_t len = any ? R.len : 0;
-    const uint32_t have = quad_have(at, len);
+    const bool whole = quad_whole(at, len);
     const uint32_t ctr = R.ctr0 + static_cast<uint32_t>(blk), x0 = R.x0, nr = R.nr;
     uint8_t *out = reinterpret_cast<uint8_t *>(R.out);
     quad_fill(lds, t0, wave, lane);
     lkeys[threadIdx.x] = kw;
-    uint32_t d = quad_load(in, at, len, have);
+    uint32_t d = quad_load(in, at, len, whole);
     __syncthreads();
     if (any) {
-        d = quad_load_rest(in, at, have, d);
+        d = quad_load_rest(in, at, len, whole, d);
         const uint32_t *ks = lkeys + 64 * wave + c;
-        d ^= nr == 10 ? quad_keystream<10>(lds, ks, c, ctr, x0) : quad_keystream<14>(lds, ks, c, ctr, x0);
-        quad_store(out, at, have, d);
+        if (nr == 10) {
+            uint32_t k[11];
+            quad_keys<10>(ks, k);
+            d ^= quad_keystream<10>(lds, k, c, ctr, x0);
+        } else {
+            uint32_t k[15];
+            quad_keys<14>(ks, k);
+            d ^= quad_keystream<14>(lds, k, c, ctr, x0);
+        }
+        quad_store(out, at, len, whole, d);
     }
     // No wave of this launch reads a slot that it installs.
     if (t == 0) {

@@ -1,8 +1,9 @@
-"""Batches of at most eight small requests (ctr_quad.hip's batch kernel) at its
-edges: the number of requests, empty ones at every place, partial words, blocks
-and workgroups, both key sizes, start counters across the 32-bit wrap, any
-address, in place, and both sides of the size at which the other kernel takes
-over; bit for bit against the CPU oracle.  The engine's resident keys too."""
+"""Batches of at most eight small requests (the batch kernels of ctr_quad.hip and
+ctr_pair.hip) at their edges: the number of requests, empty ones at every place,
+partial words, blocks and workgroups, both key sizes, start counters across the
+32-bit wrap, any address, in place, and both sides of the sizes at which the next
+kernel takes over; bit for bit against the CPU oracle.  The engine's resident
+keys too."""
 from __future__ import annotations
 
 import numpy as np
@@ -33,7 +34,7 @@ def build(torch, A, g, lengths, inplace):
         ctr0 = (0xFFFFFFFF, 0xFFFFFFF0, int(g.integers(0, 1 << 32)))[i % 3]
         reqs.append(A.Request(A.aes_expand_key(key), nonce, ctr0, x[o:o + n], y[o:o + n]))
         if n:
-            want[o:o + n] = oracle.ctr(key, nonce, ctr0, data[o:o + n])
+            want[o:o + n] = oracle.ctr(key, nonce, ctr0, data[o:o + n], threads=0)
     return reqs, y, want
 
 
@@ -47,7 +48,9 @@ def test_small_batches_match_oracle(inplace):
     import paper_2607_02630_amd as A
     g = np.random.default_rng(11 + inplace)
     most = 1024 * limit(torch)
-    for lengths in [*LENGTHS, [most], [most - 1024, 1], [most - 1024, 1025], [most // 8] * 8, [most // 8 + 1] * 8]:
+    for lengths in [*LENGTHS, [most], [most - 1024, 1], [most - 1024, 1025], [most // 8] * 8, [most // 8 + 1] * 8,
+                    [2 * most], [2 * most - 9, 1], [0, 2 * most - 4096, 0, 4095], [2 * most - 4096, 4097],
+                    [most // 4] * 8, [most // 4 - 5] * 8]:
         log(f"quad batch: {lengths}, in place {inplace}")
         reqs, y, want = build(torch, A, g, lengths, inplace)
         A.aes_ctr_crypt_batch(reqs)
@@ -57,11 +60,11 @@ def test_small_batches_match_oracle(inplace):
 
 
 def test_explicit_grid():
-    """A grid of one workgroup takes two workgroups' worth of quads; more goes to the other kernel."""
+    """A grid of one workgroup takes two workgroups of quads or one of pairs; more goes to the third kernel."""
     torch = torch_cuda()
     import paper_2607_02630_amd as A
     g = np.random.default_rng(5)
-    for lengths in ([2048], [1024, 1024], [1024, 1024, 1], [2049]):
+    for lengths in ([2048], [1024, 1024], [1024, 1024, 1], [2049], [4095], [4097], [4096, 1]):
         log(f"quad batch: {lengths}, grid 1")
         reqs, y, want = build(torch, A, g, lengths, False)
         A.aes_ctr_crypt_batch(reqs, cfg=A.batch_cfg(grid=1))
@@ -79,11 +82,11 @@ def test_engine_reuses_resident_keys():
     with A.Engine(key_slots=2) as eng:
         for step in range(24):
             i = int(g.integers(0, 3))
-            n = int(g.integers(1, 5000))
+            n = int(g.integers(1, 5000)) + (600_000 if step % 4 == 3 else 0)
             nonce, ctr0 = g.bytes(12), int(g.integers(0, 1 << 32))
             data = g.integers(0, 256, size=n, dtype=np.uint8)
             x = torch.from_numpy(data).cuda()
             y = torch.empty_like(x)
             torch.cuda.synchronize()
             eng.wait(eng.submit(A.Request(scheds[i], nonce, ctr0, x, y)))
-            assert np.array_equal(y.cpu().numpy(), oracle.ctr(keys[i], nonce, ctr0, data)), (step, i, n)
+            assert np.array_equal(y.cpu().numpy(), oracle.ctr(keys[i], nonce, ctr0, data, threads=0)), (step, i, n)
