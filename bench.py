@@ -651,8 +651,8 @@ def _median(xs):
 
 def batch_leg(torch, A, W, reps=5):
     """4096 requests, log-uniform 4 KiB..8 MiB, mixed AES-128/256 keys, own
-    nonce and counter each: one aes_ctr_crypt_batch (captured graph: upload
-    of the descriptor table + one persistent kernel) vs 4096 aes_ctr_crypt
+    nonce and counter each: one aes_ctr_crypt_batch (upload of the
+    descriptor table + one persistent kernel) vs 4096 aes_ctr_crypt
     launches (eager, graph-replayed) and vs synchronising after each."""
     import numpy as np
     import oracle

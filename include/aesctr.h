@@ -192,14 +192,14 @@ typedef struct {
 /* Encrypt n requests with one persistent kernel launch over a device
  * descriptor table (the shape of the paper's job queue, Listing 1, with every
  * job handed to the device at once).  The descriptors, schedules and tile
- * index are staged in pinned host memory and copied by a node of a captured
- * HIP graph, replayed on each call.  A batch of at most 8 requests skips the
+ * index are staged in pinned host memory and uploaded by a small kernel ahead
+ * of it.  A batch of at most 8 requests skips the
  * table: its records travel in the kernel's argument block, so no copy
  * precedes the launch.  Each request's output equals
  * aes_ctr_crypt on that request alone.  n == 0 is a no-op.
  * Errors: AES_EINVAL (null desc with n > 0, null sched, flags != 0, a
- * stream that is being captured -- the call launches its own graph and its
- * staging is rewritten by later calls), AES_ERANGE, AES_EOVERLAP (per
+ * stream that is being captured -- the call's staging is rewritten by later
+ * calls), AES_ERANGE, AES_EOVERLAP (per
  * request), AES_ENOMEM, AES_EDEVICE.  Thread-safe for calls on distinct
  * streams; calls on one stream are serialised. */
 int aes_ctr_crypt_batch(const aes_ctr_desc_t *desc, size_t n, void *stream);
@@ -208,8 +208,8 @@ int aes_ctr_crypt_batch(const aes_ctr_desc_t *desc, size_t n, void *stream);
  * multiple of 1024), wg_size, grid, blocks_per_lane; zero = default (tiles
  * sized to the batch, about sixteen per CU within 2-64 KiB; 2 blocks per
  * lane; 1024-thread workgroups, one per CU; a tune cache may override).
- * use_graph: 1 = captured graph, 0 = plain copy + launch; a call without cfg
- * uses the graph; batches of at most 8 requests use neither: their kernel
+ * use_graph: 1 = a captured graph of upload and kernel, 0 = two plain launches;
+ * a call without cfg launches plainly, which is the faster; batches of at most 8 requests use neither: their kernel
  * has 256-thread workgroups, a wave per tile up to twice `grid` workgroups,
  * and takes tile_bytes and blocks_per_lane from cfg like the table kernel, or,
  * where that holds it all, runs with four lanes per block (workgroups of 64

@@ -273,7 +273,7 @@ struct LaunchSpec {
 // Host side of the batch path (batch.cpp).  make_batch_record expands one
 // validated request into its record.  launch_spec stages one launch (at most
 // kMaxBatch requests) on the (device, stream) context and launches it through
-// the slot's captured graph or a plain copy + launch, or, with allow_small and
+// the slot's captured graph or two plain launches, or, with allow_small and
 // at most kSmallBatch requests, in the kernel's argument block.
 int check_desc(const aes_ctr_desc_t &d);
 // Tile size for a batch of batch_bytes payload bytes (about 16 tiles per CU,

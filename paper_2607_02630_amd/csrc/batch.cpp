@@ -291,8 +291,8 @@ int take_slot(BatchCtx *c, int *slot)
 }
 
 // Uploads the first `bytes` of staging slot `slot` into the device table and
-// launches the batch kernel on st, through the slot's captured graph or a
-// plain copy + launch, then marks the slot busy until that work finishes.
+// launches the batch kernel on st, as two plain launches or through the slot's
+// captured graph of them, then marks the slot busy until that work finishes.
 int submit_slot(BatchCtx *c, int slot, size_t bytes, hipStream_t st, int grid, int bpl, bool use_graph)
 {
     int rc;
@@ -477,8 +477,13 @@ extern "C" int aes_ctr_crypt_batch_cfg(const aes_ctr_desc_t *desc, size_t n, con
         total_bytes += scan[p].bytes;
     }
     // Tile size 0 = sized to the batch (batch_tile_bytes); two blocks per
-    // lane unless the tune cache says otherwise.
-    BatchShape sh{0, 1024, 0, batch_blocks_per_lane(), 1};
+    // lane unless the tune cache says otherwise.  Two plain launches (upload,
+    // kernel): replaying a graph of them, which paid while the upload was a copy
+    // of the runtime's, costs more at every size.  us per call up to its end (and
+    // back to back), graph against plain: 9 requests of 0.1-1 KB 38.0 (23.4) and
+    // 22.4 (15.2), 64 of 4 KiB-1 MiB 42.8 (31.7) and 33.6 (24.6), 1000 of 4-64 KiB
+    // 82.3 (55.0) and 68.0 (42.0), 4096 of them 230 (138) and 204 (131).
+    BatchShape sh{0, 1024, 0, batch_blocks_per_lane(), 0};
     if (cfg) {
         if (cfg->tile_bytes < 0 || (cfg->tile_bytes && (cfg->tile_bytes % 1024 != 0 || cfg->tile_bytes > (1 << 26))))
             return AES_EINVAL;
