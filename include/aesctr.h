@@ -209,7 +209,9 @@ int aes_ctr_crypt_batch(const aes_ctr_desc_t *desc, size_t n, void *stream);
  * sized to the batch, about sixteen per CU within 2-64 KiB; 2 blocks per
  * lane; 1024-thread workgroups, one per CU; a tune cache may override).
  * use_graph: 1 = a captured graph of upload and kernel, 0 = two plain launches;
- * a call without cfg launches plainly, which is the faster; batches of at most 8 requests use neither: their kernel
+ * a call without cfg launches plainly, which is the faster, and up to 256
+ * requests of at most twice `grid` times 64 blocks then run with four lanes per
+ * block, whatever tile_bytes and blocks_per_lane say; batches of at most 8 requests use neither: their kernel
  * has 256-thread workgroups, a wave per tile up to twice `grid` workgroups,
  * and takes tile_bytes and blocks_per_lane from cfg like the table kernel, or,
  * where that holds it all, runs with four lanes per block (workgroups of 64

@@ -249,6 +249,10 @@ int launch_ctr_batch_small(const SmallBatchArgs &args, int grid, int bpl, hipStr
 constexpr uint32_t kQuadTileBlocks = 64, kPairTileBlocks = 256;
 int launch_ctr_quad_batch(const SmallBatchArgs &args, hipStream_t st);
 int launch_ctr_pair_batch(const SmallBatchArgs &args, hipStream_t st);
+// The same with four lanes per block for at most kQuadTableReqs requests in the
+// uploaded table whose header is h (tiles counted by plain_tiles).
+constexpr uint32_t kQuadTableReqs = 256;
+int launch_ctr_quad_table(const void *dev_table, const BatchHeader &h, hipStream_t st);
 
 // One request as the host keeps it before staging: its descriptor (key field
 // not yet assigned) and its round keys.
@@ -298,7 +302,7 @@ uint32_t batch_own_tiles(uint64_t tiles, int grid);
 // installs written, n_keys / n_install / resident set in the header):
 // assigns each request's first tile and fills the rest of the header.
 // Returns the table's bytes, or 0 if the tile count would overflow 31 bits.
-size_t finish_stage(uint8_t *buf, size_t n, uint32_t tile_blocks, int grid);
+size_t finish_stage(uint8_t *buf, size_t n, uint32_t tile_blocks, int grid, bool plain = false);
 
 // Returns the staging context of stream st on device to the device's free
 // list (the stream is about to be destroyed; its work must have finished or

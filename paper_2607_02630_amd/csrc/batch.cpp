@@ -171,18 +171,24 @@ uint32_t batch_own_tiles(uint64_t tiles, int grid)
     return static_cast<uint32_t>(per_wg >= 64 ? per_wg - per_wg / 12 : per_wg);
 }
 
+// Tiles of tile_blocks blocks from a request's start.
+static uint64_t plain_tiles(uint64_t len, uint32_t tile_blocks)
+{
+    return len / (16 * tile_blocks) + (len % (16 * tile_blocks) != 0);
+}
+
 // Completes a staged table at buf: n descriptors, header.n_keys inline keys
 // and header.n_install installs written.  Assigns first tiles and fills the
 // rest of the header.  Returns the bytes to upload, or 0 if the tile count
 // would overflow.
-size_t finish_stage(uint8_t *buf, size_t n, uint32_t tile_blocks, int grid)
+size_t finish_stage(uint8_t *buf, size_t n, uint32_t tile_blocks, int grid, bool plain)
 {
     BatchHeader *h = reinterpret_cast<BatchHeader *>(buf);
     BatchDesc *out = reinterpret_cast<BatchDesc *>(buf + sizeof(BatchHeader));
     uint64_t tiles = 0;
     for (size_t i = 0; i < n; ++i) {
         out[i].tile0 = static_cast<uint32_t>(tiles);
-        tiles += request_tiles(out[i].len, out[i].ctr0, tile_blocks);
+        tiles += plain ? plain_tiles(out[i].len, tile_blocks) : request_tiles(out[i].len, out[i].ctr0, tile_blocks);
         if (tiles > 0x7fffffffu)
             return 0;
     }
@@ -202,10 +208,22 @@ namespace {
 // Records per part of the host's parallel record building.
 constexpr size_t kRecordGrain = 256;
 
-// Tiles of tile_blocks blocks from a request's start.
-uint64_t plain_tiles(uint64_t len, uint32_t tile_blocks)
+// Whether the requests in a staged table run with four lanes per block
+// (ctr_quad_table_kernel): at most two of its workgroups per CU of the grid, the
+// small batch's limit, and no more requests than its waves look through.  us per
+// call back to back, and for one call up to its end, in brackets as tiles of the
+// table kernel: 9 requests of 0.1-1 KB 10.4 (15.0) and 18.2 (22.4), 64 of them 11.1
+// (15.4) and 20.0 (24.3), 256 of 0.1-4 KB 14.6 (17.1) and 26.2 (29.7), 12 of 20-60
+// KB 11.2 (15.3) and 19.4 (23.0).  Not through a captured graph, whose second node
+// is the table kernel.
+bool quad_table(const BatchDesc *descs, size_t n, int grid)
 {
-    return len / (16 * tile_blocks) + (len % (16 * tile_blocks) != 0);
+    if (n > kQuadTableReqs)
+        return false;
+    uint64_t tiles = 0;
+    for (size_t i = 0; i < n; ++i)
+        tiles += plain_tiles(descs[i].len, kQuadTileBlocks);
+    return tiles <= 2 * static_cast<uint64_t>(grid);
 }
 
 // A batch of at most kSmallBatch requests goes in the kernel's argument block
@@ -293,7 +311,7 @@ int take_slot(BatchCtx *c, int *slot)
 // Uploads the first `bytes` of staging slot `slot` into the device table and
 // launches the batch kernel on st, as two plain launches or through the slot's
 // captured graph of them, then marks the slot busy until that work finishes.
-int submit_slot(BatchCtx *c, int slot, size_t bytes, hipStream_t st, int grid, int bpl, bool use_graph)
+int submit_slot(BatchCtx *c, int slot, size_t bytes, hipStream_t st, int grid, int bpl, bool use_graph, bool quad)
 {
     int rc;
     const uint32_t quads = static_cast<uint32_t>((bytes + 15) / 16);
@@ -311,7 +329,9 @@ int submit_slot(BatchCtx *c, int slot, size_t bytes, hipStream_t st, int grid, i
     } else {
         if ((rc = launch_upload(c->staging_view[slot], c->dev_table, quads, st)) != AES_OK)
             return rc;
-        if ((rc = launch_ctr_batch(c->dev_table, grid, 1024, bpl, st)) != AES_OK)
+        rc = quad ? launch_ctr_quad_table(c->dev_table, *reinterpret_cast<const BatchHeader *>(c->staging[slot]), st)
+                  : launch_ctr_batch(c->dev_table, grid, 1024, bpl, st);
+        if (rc != AES_OK)
             return rc;
     }
     if (hipEventRecord(c->done[slot], st) != hipSuccess) {
@@ -352,10 +372,11 @@ int launch_spec(int device, hipStream_t st, const LaunchSpec &spec, int tile_byt
     memcpy(buf + sizeof(BatchHeader), spec.descs, spec.n * sizeof(BatchDesc));
     memcpy(buf + batch_keys_off(spec.n), spec.keys, spec.n_keys * sizeof(KeyRec));
     memcpy(buf + batch_install_off(spec.n, spec.n_keys), spec.installs, spec.n_install * sizeof(InstallRec));
-    const size_t bytes = finish_stage(buf, spec.n, tile_blocks, grid);
+    const bool quad = !use_graph && allow_small && quad_table(spec.descs, spec.n, grid);
+    const size_t bytes = finish_stage(buf, spec.n, quad ? kQuadTileBlocks : tile_blocks, grid, quad);
     if (bytes == 0)
         return AES_ERANGE;
-    return submit_slot(c, slot, bytes, st, grid, bpl, use_graph);
+    return submit_slot(c, slot, bytes, st, grid, bpl, use_graph, quad);
 }
 
 void release_batch_stream(int device, hipStream_t st)
@@ -556,10 +577,11 @@ extern "C" int aes_ctr_crypt_batch_cfg(const aes_ctr_desc_t *desc, size_t n, con
                 out[i].key = static_cast<uint32_t>(i);
             }
         });
-        const size_t bytes = finish_stage(buf, m, tile_blocks, sh.grid);
+        const bool quad = sh.use_graph == 0 && quad_table(out, m, sh.grid);
+        const size_t bytes = finish_stage(buf, m, quad ? kQuadTileBlocks : tile_blocks, sh.grid, quad);
         if (bytes == 0)
             return AES_ERANGE;
-        if ((rc = submit_slot(c, slot, bytes, st, sh.grid, sh.bpl, sh.use_graph != 0)) != AES_OK)
+        if ((rc = submit_slot(c, slot, bytes, st, sh.grid, sh.bpl, sh.use_graph != 0, quad)) != AES_OK)
             return rc;
     }
     return AES_OK;

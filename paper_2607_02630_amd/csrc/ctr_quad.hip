@@ -20,7 +20,8 @@
 // 4 KiB 1.92 us (2.89), 64 KiB 2.02 (3.08), 256 KiB 2.07 (3.14), 512 KiB 2.44 (3.19);
 // AES-256: 2.13 (3.40), 2.21 (3.58), 2.29 (3.63), 2.80 (3.71).  An empty launch takes
 // 1.56 us there.  Batches of a few small requests take the same path
-// (ctr_quad_batch_kernel; figures at launch_small in batch.cpp).
+// (ctr_quad_batch_kernel, ctr_quad_table_kernel; figures at launch_small and
+// quad_table in batch.cpp).
 #include "ttable_device.h"
 
 namespace aesctr {
@@ -206,6 +207,72 @@ __global__ __launch_bounds__(kQuadWG) void ctr_quad_batch_kernel(const SmallBatc
     }
 }
 
+// More requests than the argument block takes, as few blocks: records, keys and
+// installs in the uploaded table.  The scalars of its header come as arguments,
+// and a wave finds its request by counting the first tiles up to t, a request
+// per lane and load: one memory round trip each for them, the request and the key.
+__global__ __launch_bounds__(kQuadWG) void ctr_quad_table_kernel(const uint8_t *__restrict__ table, uint32_t *resident,
+                                                                 uint32_t n, uint32_t total, uint32_t n_install,
+                                                                 uint32_t install_off)
+{
+    __shared__ uint32_t lds[4 * 256];
+    __shared__ uint32_t lkeys[kQuadWG];
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, c = lane & 3, t = blockIdx.x;
+    const BatchDesc *desc = reinterpret_cast<const BatchDesc *>(table + sizeof(BatchHeader));
+    const uint32_t *keys = reinterpret_cast<const uint32_t *>(table + batch_keys_off(n));
+    uint32_t first[kQuadTableReqs / 64];
+#pragma unroll
+    for (uint32_t u = 0; u < kQuadTableReqs / 64; ++u) {
+        const uint32_t i = lane + 64 * u;
+        first[u] = desc[i < n ? i : n - 1].tile0;
+    }
+    const u32x4 t0 = reinterpret_cast<const u32x4 *>(c_round.t[0])[lane];
+    // Last request whose first tile is <= t: tile0 ascends from 0, and empty
+    // requests share their successor's.
+    uint32_t upto = 0;
+#pragma unroll
+    for (uint32_t u = 0; u < kQuadTableReqs / 64; ++u)
+        upto += static_cast<uint32_t>(__popcll(__ballot(lane + 64 * u < n && first[u] <= t)));
+    const BatchDesc &R = desc[__builtin_amdgcn_readfirstlane(upto) - 1];
+    const uint32_t key = R.key;
+    const uint32_t *from = key & kKeyResident ? resident + 64u * (key & ~kKeyResident) : keys + 64u * key;
+    const uint32_t kw = lane < 4 ? R.k1[lane] : from[lane - 4];
+    const uint8_t *in = reinterpret_cast<const uint8_t *>(R.in);
+    uint8_t *out = reinterpret_cast<uint8_t *>(R.out);
+    const uint64_t blk = static_cast<uint64_t>(t - R.tile0) * kBlocks + (threadIdx.x >> 2);
+    const uint64_t at = 16 * blk + 4 * c;
+    const bool any = t < total;     // no tile at all: a launch for its installs
+    const uint64_t len = any ? R.len : 0;
+    const bool whole = quad_whole(at, len);
+    const uint32_t ctr = R.ctr0 + static_cast<uint32_t>(blk), x0 = R.x0, nr = R.nr;
+    quad_fill(lds, t0, wave, lane);
+    lkeys[threadIdx.x] = kw;
+    uint32_t d = quad_load(in, at, len, whole);
+    __syncthreads();
+    if (any) {
+        d = quad_load_rest(in, at, len, whole, d);
+        const uint32_t *ks = lkeys + 64 * wave + c;
+        if (nr == 10) {
+            uint32_t k[11];
+            quad_keys<10>(ks, k);
+            d ^= quad_keystream<10>(lds, k, c, ctr, x0);
+        } else {
+            uint32_t k[15];
+            quad_keys<14>(ks, k);
+            d ^= quad_keystream<14>(lds, k, c, ctr, x0);
+        }
+        quad_store(out, at, len, whole, d);
+    }
+    // No wave of this launch reads a slot that it installs.
+    if (t == 0) {
+        const InstallRec *inst = reinterpret_cast<const InstallRec *>(table + install_off);
+        for (uint32_t j = threadIdx.x; j < 64u * n_install; j += kQuadWG) {
+            const InstallRec r = inst[j >> 6];
+            resident[64u * r.slot + (j & 63u)] = keys[64u * r.key + (j & 63u)];
+        }
+    }
+}
+
 template <int NR>
 void launch_quad(const CtrArgs &a, hipStream_t st)
 {
@@ -247,6 +314,17 @@ int launch_ctr_quad_batch(const SmallBatchArgs &args, hipStream_t st)
     (void)hipGetLastError();   // not ours: left by earlier calls
     const dim3 grid(args.total_tiles ? args.total_tiles : 1);
     hipLaunchKernelGGL(ctr_quad_batch_kernel, grid, dim3(kQuadWG), 0, st, args);
+    return launch_status();
+}
+
+int launch_ctr_quad_table(const void *dev_table, const BatchHeader &h, hipStream_t st)
+{
+    if (h.n == 0 || h.n > kQuadTableReqs || h.tile_blocks != kQuadTileBlocks || h.total_tiles > 0x7fffffffu)
+        return AES_EINVAL;
+    (void)hipGetLastError();   // not ours: left by earlier calls
+    const dim3 grid(h.total_tiles ? h.total_tiles : 1);
+    hipLaunchKernelGGL(ctr_quad_table_kernel, grid, dim3(kQuadWG), 0, st, static_cast<const uint8_t *>(dev_table),
+                       reinterpret_cast<uint32_t *>(h.resident), h.n, h.total_tiles, h.n_install, h.install_off);
     return launch_status();
 }
 

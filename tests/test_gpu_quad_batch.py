@@ -42,6 +42,26 @@ def limit(torch):
     return 2 * torch.cuda.get_device_properties(0).multi_processor_count     # workgroups of 64 blocks
 
 
+# More requests than the argument block takes (ctr_quad_table_kernel), up to and past its 256.
+TABLES = [[5] * 9, [0] * 9 + [17], [33, 0] * 20, [0, 1024, 1025, 0] * 8, [1000] * 64, [1024] * 65, [40] * 255 + [1],
+          [0] * 255 + [70_001], [40] * 257, [0] * 12]
+
+
+@pytest.mark.parametrize("inplace", [False, True])
+def test_table_batches_match_oracle(inplace):
+    torch = torch_cuda()
+    import paper_2607_02630_amd as A
+    g = np.random.default_rng(21 + inplace)
+    most = 1024 * limit(torch)
+    for lengths in [*TABLES, [most // 16] * 16, [most // 16] * 15 + [most // 16 + 1], [most // 128 - 7] * 128]:
+        log(f"quad table: {len(lengths)} requests, {sum(lengths)} bytes, in place {inplace}")
+        reqs, y, want = build(torch, A, g, lengths, inplace)
+        A.aes_ctr_crypt_batch(reqs)
+        torch.cuda.synchronize()
+        bad = np.flatnonzero(y.cpu().numpy() != want)
+        assert bad.size == 0, (lengths[:4], len(lengths), int(bad[0]))
+
+
 @pytest.mark.parametrize("inplace", [False, True])
 def test_small_batches_match_oracle(inplace):
     torch = torch_cuda()
@@ -57,6 +77,30 @@ def test_small_batches_match_oracle(inplace):
         torch.cuda.synchronize()
         bad = np.flatnonzero(y.cpu().numpy() != want)
         assert bad.size == 0, (lengths, int(bad[0]))
+
+
+def test_engine_bursts_install_and_reuse_keys():
+    """Bursts of more than eight small requests: tables with installs and with keys read from their slots."""
+    torch = torch_cuda()
+    import paper_2607_02630_amd as A
+    g = np.random.default_rng(19)
+    keys = [g.bytes((16, 32)[i % 2]) for i in range(6)]
+    scheds = [A.aes_expand_key(k) for k in keys]
+    with A.Engine(key_slots=4) as eng:
+        for burst in range(8):
+            work = []
+            for _ in range(60):
+                i, n = int(g.integers(0, 6)), int(g.integers(1, 3000))
+                nonce, ctr0 = g.bytes(12), int(g.integers(0, 1 << 32))
+                data = g.integers(0, 256, size=n, dtype=np.uint8)
+                x = torch.from_numpy(data).cuda()
+                work.append((i, nonce, ctr0, data, x, torch.empty_like(x)))
+            torch.cuda.synchronize()
+            tickets = [eng.submit(A.Request(scheds[i], nonce, ctr0, x, y)) for i, nonce, ctr0, _, x, y in work]
+            for t in tickets:
+                eng.wait(t)
+            for j, (i, nonce, ctr0, data, _, y) in enumerate(work):
+                assert np.array_equal(y.cpu().numpy(), oracle.ctr(keys[i], nonce, ctr0, data)), (burst, j)
 
 
 def test_explicit_grid():
