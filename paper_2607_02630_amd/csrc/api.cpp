@@ -103,6 +103,67 @@ bool tuned_for(const TuneEntry &te, uint64_t blocks, uint64_t cus)
     return (blocks + pass - 1) / pass <= (tuned + pass - 1) / pass;
 }
 
+void take_entry(const TuneEntry &te, int num_cus, Shape *sh)
+{
+    sh->bpl = te.bpl;
+    sh->wg = te.wg;
+    sh->copies = te.copies;
+    sh->tables = te.tables ? te.tables : (te.copies == 64 ? 2 : 4);
+    sh->grid = te.grid_per_cu * num_cus;
+    if (te.first >= kFirstWave0 && te.first <= kFirstFull &&
+        first_chunk_mode_ok(te.first, sh->copies, sh->tables, sh->bpl, sh->wg))
+        sh->wave_groups = te.first;
+}
+
+// The shape that a caller's explicit fields change where they name another than the
+// default: one of the T-table kernel's
+// own (ctr_ttable.hip), which every combination of them was built for.  The
+// default's shapes above 16 MiB belong to another kernel (four tables, 1024
+// threads): on top of those a mode or a block count alone would name a shape
+// that does not exist, and 256 threads would run one small workgroup per CU
+// (64 MiB in 86 us; from this base 49).
+Shape explicit_base(int key_bits, uint64_t len, const DeviceInfo &di)
+{
+    Shape sh{};
+    sh.variant = AES_VARIANT_TTABLE;
+    sh.wave_groups = -1;
+    TuneEntry te;
+    if (tune_lookup(sh.variant, key_bits, len, &te)) {
+        take_entry(te, di.num_cus, &sh);
+        if (sh.wg == 1024 && sh.bpl == 2 && sh.tables == 4 && sh.wave_groups == kFirstWave0) {
+            // An entry for the large-message kernel: the T-table kernel's best there.
+            sh.wg = key_bits == 256 ? 1024 : 512;
+            sh.bpl = key_bits == 256 ? 1 : 4;
+            sh.tables = 2;
+            sh.grid = 4 * di.num_cus;
+        }
+        return sh;
+    }
+    sh.grid = di.num_cus;
+    sh.copies = 32;
+    sh.tables = 2;
+    const uint64_t per_cu = (len / 16) / static_cast<uint64_t>(di.num_cus > 0 ? di.num_cus : 1);
+    if (per_cu >= 2048) {
+        sh.bpl = per_cu >= 4096 ? 4 : 2;
+        sh.wg = 512;
+        sh.grid = 4 * di.num_cus;
+    } else {
+        sh.bpl = per_cu >= 1024 ? 2 : 1;
+        sh.wg = per_cu >= 512 ? 512 : 256;
+        sh.wave_groups = kFirstFull;
+    }
+    return sh;
+}
+
+// Whether cfg names a part of the launch shape that is not def's.
+bool other_shape(const aes_launch_cfg_t &cfg, const Shape &def)
+{
+    auto other = [](int32_t field, int have) { return field != 0 && field != have; };
+    return other(cfg.blocks_per_lane, def.bpl) || other(cfg.wg_size, def.wg) || other(cfg.grid, def.grid) ||
+           other(cfg.lds_copies, def.copies) || other(cfg.lds_tables, def.tables) ||
+           other(cfg.wave_groups, def.wave_groups == kFirstWave0 ? 3 : def.wave_groups);
+}
+
 }  // namespace
 
 Shape default_shape(int variant, int key_bits, uint64_t len, const DeviceInfo &di)
@@ -115,14 +176,7 @@ Shape default_shape(int variant, int key_bits, uint64_t len, const DeviceInfo &d
     const uint64_t blocks = (len + 15) / 16;
     if (tune_lookup(sh.variant, key_bits, len, &te) &&
         (sh.variant != AES_VARIANT_TTABLE || tuned_for(te, blocks, cus))) {
-        sh.bpl = te.bpl;
-        sh.wg = te.wg;
-        sh.copies = te.copies;
-        sh.tables = te.tables ? te.tables : (te.copies == 64 ? 2 : 4);
-        sh.grid = te.grid_per_cu * di.num_cus;
-        if (te.first >= kFirstWave0 && te.first <= kFirstFull &&
-            first_chunk_mode_ok(te.first, sh.copies, sh.tables, sh.bpl, sh.wg))
-            sh.wave_groups = te.first;
+        take_entry(te, di.num_cus, &sh);
     } else if (sh.variant == AES_VARIANT_TTABLE) {
         // The LDS holds only T0 and T2 (32 copies, 64 KiB): half the table
         // fill of four tables, for about 15% more VALU work per block, and
@@ -272,7 +326,8 @@ int check_cfg(const aes_launch_cfg_t *cfg, int *variant)
 Shape resolve_shape(int variant, int key_bits, uint64_t len, const aes_launch_cfg_t *cfg, const DeviceInfo &di)
 {
     Shape sh = default_shape(variant, key_bits, len, di);
-    const Shape def = sh;
+    if (cfg && sh.variant == AES_VARIANT_TTABLE && other_shape(*cfg, sh))
+        sh = explicit_base(key_bits, len, di);
     if (cfg) {
         if (cfg->blocks_per_lane) sh.bpl = cfg->blocks_per_lane;
         if (cfg->wg_size) sh.wg = cfg->wg_size;
@@ -299,10 +354,7 @@ Shape resolve_shape(int variant, int key_bits, uint64_t len, const aes_launch_cf
     // Per-wave first-chunk group constants pay off when two workgroups with
     // the 64 KiB image share each CU (8 MiB AES-128: 7.64-7.69 against
     // 7.74-7.78 us); other shapes fall back to wave 0 computing them.
-    // The default's mode holds for its own chunks; with one workgroup per CU it
-    // also stays where cfg changes them.
-    const bool same = sh.bpl == def.bpl && sh.wg == def.wg && sh.tables == def.tables;
-    const int tuned = same || def.grid <= di.num_cus ? def.wave_groups : -1;
+    const int tuned = sh.wave_groups;
     sh.wave_groups = kFirstWave0;
     if (sh.variant == AES_VARIANT_TTABLE) {
         if (cfg && cfg->wave_groups)
