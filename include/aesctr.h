@@ -132,10 +132,11 @@ typedef enum {
  *                    shape is not built for is AES_EINVAL.  Output (from
  *                    aes_ctr_launch_shape): the mode used, 1, 2, or 0 for
  *                    wave 0.
- * A message of at most 256 blocks of 16 bytes per CU whose shape is 256 threads,
- * 1 block per lane, 2 tables of 32 copies, mode 2 and a grid that holds it in one
- * chunk per workgroup runs with four (up to 128 blocks per CU) or two lanes per
- * block, in workgroups of 256 or 512 threads and as many as it needs. */
+ * What a call names here is what it launches.  A call that names none of them
+ * (variant apart) may run a small message, of at most 256 blocks of 16 bytes per
+ * CU whose shape is 256 threads, 1 block per lane, 2 tables of 32 copies and mode
+ * 2, with four (up to 128 blocks per CU) or two lanes per block, in workgroups of
+ * 256 or 512 threads and as many as it needs. */
 typedef struct {
     int32_t variant;
     int32_t blocks_per_lane;
@@ -162,7 +163,9 @@ int aes_ctr_crypt_cfg(const aes_sched_t *sched, const uint8_t nonce[12], uint32_
  * one of the T-table kernel's own for that size instead (its entry, or 1 x 256, 1 x 512 or
  * 2 x 512 blocks per lane and threads up to 8 MiB on 256 CUs, 4 x 512 from 16),
  * so what they name does not depend on which kernel the default call runs.  The
- * grid is clamped to the work.  All fields of *out are set (variant 1,
+ * grid is clamped to the work.  For a small message that runs with four or two
+ * lanes per block (see aes_launch_cfg_t) this is the shape that the T-table kernel
+ * would take, which the call runs when the shape is handed back to it.  All fields of *out are set (variant 1,
  * 2 or 3, never AUTO; lds_copies and lds_tables 0 for the kernels without
  * T-tables).  Host only; it
  * needs the current device's CU count.  Errors: AES_EINVAL (null out, key

@@ -148,7 +148,9 @@ def main(argv=None):
                 for kw in [dict(rule_kw)] + list(candidates(variant, args.quick)):
                     is_rule = rule is None
                     grid = kw.pop("grid")
-                    cfg = A.launch_cfg(grid=grid * cus, **kw)
+                    # The rule as a call that names no shape runs it, which may be
+                    # with several lanes per block; the candidates as they are named.
+                    cfg = A.launch_cfg(variant=variant) if is_rule else A.launch_cfg(grid=grid * cus, **kw)
                     A.aes_ctr_crypt(sched, nonce, 1, ins[0], outs[0], cfg=cfg)
                     torch.cuda.synchronize()
                     digest = hashlib.sha256(outs[0].cpu().numpy().tobytes()).hexdigest()
@@ -165,8 +167,7 @@ def main(argv=None):
                 # size can catch clocks still ramping) and keeps the faster of
                 # its two; it stays unless a candidate beats it by 1% or more
                 # (closer than that is within run-to-run noise).
-                rule_cfg = A.launch_cfg(**{k: (v * cus if k == "grid" else v) for k, v in rule[1].items()})
-                again = time_shape(torch, A, sched, nonce, ins, outs, rule_cfg, size)
+                again = time_shape(torch, A, sched, nonce, ins, outs, A.launch_cfg(variant=variant), size)
                 if again < rule[0]:
                     rule = (again, rule[1])
                     if again < best[0]:

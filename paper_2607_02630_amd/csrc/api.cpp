@@ -155,6 +155,13 @@ Shape explicit_base(int key_bits, uint64_t len, const DeviceInfo &di)
     return sh;
 }
 
+// Whether cfg names any part of the launch shape.
+bool names_shape(const aes_launch_cfg_t *cfg)
+{
+    return cfg && (cfg->blocks_per_lane || cfg->wg_size || cfg->grid || cfg->lds_copies || cfg->lds_tables ||
+                   cfg->wave_groups);
+}
+
 // Whether cfg names a part of the launch shape that is not def's.
 bool other_shape(const aes_launch_cfg_t &cfg, const Shape &def)
 {
@@ -435,10 +442,14 @@ extern "C" int aes_ctr_crypt_cfg(const aes_sched_t *sched, const uint8_t nonce[1
     memcpy(a.rk, km.rk, sizeof(a.rk));
     if (sh.variant == AES_VARIANT_BITSLICE)
         return launch_ctr_bitslice(a, km.nr, sh, st);
-    if (quad_shape(sh, len, di.num_cus))
-        return launch_ctr_quad(a, km.nr, st);
-    if (pair_shape(sh, len, di.num_cus))
-        return launch_ctr_pair(a, km.nr, st);
+    // Quads and pairs of lanes have grids and workgroups of their own, so they
+    // are for callers who leave the shape to the library.
+    if (!names_shape(cfg)) {
+        if (quad_shape(sh, len, di.num_cus))
+            return launch_ctr_quad(a, km.nr, st);
+        if (pair_shape(sh, len, di.num_cus))
+            return launch_ctr_pair(a, km.nr, st);
+    }
     if (bulk_shape(sh, len))
         return launch_ctr_bulk(a, km.nr, sh, st);
     return launch_ctr_ttable(a, km.nr, sh, st);

@@ -239,7 +239,7 @@ void launch_pair(const CtrArgs &a, hipStream_t st)
 // beside the first.  Pairs against one lane per block, AES-128 and AES-256: 1 MiB
 // 2.79 us against 3.26 and 3.12 against 3.81; 1.1 MB 3.85 against 3.45 and 4.37
 // against 4.06.  Against quads: 512 KiB 2.73 against 2.44, 800,000 bytes 2.78
-// against 3.18.  A grid that is smaller than the work is the caller's choice and is kept.
+// against 3.18.  Asked for calls that name no shape, as quad_shape is.
 bool pair_shape(const Shape &sh, uint64_t len, int num_cus)
 {
     const uint64_t blocks = (len + 15) / 16;

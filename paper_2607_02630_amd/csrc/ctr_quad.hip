@@ -287,7 +287,7 @@ void launch_quad(const CtrArgs &a, hipStream_t st)
 // there the bank conflicts of the one table copy cost what the shorter chain
 // saves.  Quads against one lane per block, AES-128 and AES-256: 512 KiB 2.44 us
 // against 3.19 and 2.80 against 3.71; 1 MiB 3.28 against 3.26 and 4.02 against 3.81.
-// A grid that is smaller than the work is the caller's choice and is kept.
+// Asked for calls that name no shape; a tuned grid that is smaller than the work keeps its kernel.
 bool quad_shape(const Shape &sh, uint64_t len, int num_cus)
 {
     const uint64_t blocks = (len + 15) / 16;

@@ -81,3 +81,17 @@ def test_fields_that_name_the_default_change_nothing(exe):
             bpl, wg, grid, copies, tables, mode = default[2]
             for kw in (dict(bpl=bpl), dict(wg=wg, tables=tables), dict(copies=copies), dict(mode=mode or 3)):
                 assert ask(exe, [(bits, n, kw)])[0] == default, (bits, n, kw)
+
+
+def test_several_lanes_per_block_only_for_callers_who_name_no_shape(exe):
+    """Those kernels launch workgroups of their own, more than an explicit grid holds."""
+    for bits in (128, 256):
+        for n, kernel in ((1, "quad"), (65536, "quad"), (512 * 1024, "quad"), (512 * 1024 + 1, "pair"), (MiB, "pair"),
+                          (MiB + 1, "ttable")):
+            assert ask(exe, [(bits, n, {})])[0][:2] == (0, kernel)
+            assert ask(exe, [(bits, n, dict(variant=1))])[0][:2] == (0, kernel)
+            named = dict(variant=1, bpl=1, wg=256, copies=32, tables=2, mode=2)
+            for kw in (dict(grid=256), dict(wg=256), dict(mode=2), dict(tables=2), named, dict(named, grid=1000)):
+                rc, got, shape = ask(exe, [(bits, n, kw)])[0]
+                assert (rc, got) == (0, "ttable"), (bits, n, kw, got)
+                assert shape[2] <= kw.get("grid", 256 + 1), (bits, n, kw, shape)
