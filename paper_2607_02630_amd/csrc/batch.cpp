@@ -1,18 +1,24 @@
-// batch.cpp -- aes_ctr_crypt_batch: descriptor table staging and the
-// captured-graph launch.
+// batch.cpp -- aes_ctr_crypt_batch: descriptor table staging and launch.
 //
-// Per (device, stream) the library keeps a context: a device table (header +
-// up to kMaxBatch descriptors, their inline keys and key installs) and a ring
-// of pinned host staging slots, each with an executable HIP graph of two
-// nodes -- the kernel that copies that slot into the table, then the
-// persistent batch kernel.  A call fills a free slot, sets its graph's copy
-// size, and launches the graph on the caller's stream; nothing is
-// re-captured between calls.  A slot (and its graph) is reused only after the
-// event recorded behind its last launch completes, so no update touches a
-// graph still in flight.  The tile counter the kernel claims work from is
-// part of every upload (0), so no memset node is needed.  The call cannot
-// itself be captured into a caller's graph (its staging would be rewritten
-// by later calls): on a capturing stream it returns AES_EINVAL.
+// Per (device, stream) the library keeps a context: a ring of slots, each a
+// pinned host buffer for one launch's table (header + up to kMaxBatch
+// descriptors, their inline keys and key installs) and the device table it is
+// uploaded to.  A call fills a free slot and launches two kernels on the
+// caller's stream: one that copies the slot into its table, then the batch
+// kernel over it; with use_graph they are the two nodes of an executable HIP
+// graph that the slot keeps, whose copy size is set before each launch (nothing
+// is re-captured between calls).
+//
+// A slot, with its table and graph, is used again only after the event recorded
+// behind its last launch has been waited for on the host.  Nothing else orders
+// calls, so it does not matter which queue a stream handle stands for:
+// hipStreamPerThread is one value and a stream of its own in every thread, and a
+// new stream may get the address of a destroyed one whose work still runs.
+//
+// The tile counter the kernel claims work from is part of every upload (0), so
+// no memset node is needed.  The call cannot itself be captured into a caller's
+// graph (its staging would be rewritten by later calls): on a capturing stream
+// it returns AES_EINVAL.
 #include <algorithm>
 #include <map>
 #include <memory>
@@ -48,7 +54,7 @@ struct SlotGraph {
 struct BatchCtx {
     std::mutex mu;
     int device = -1;
-    void *dev_table = nullptr;
+    void *dev_table[kSlots] = {};
     uint8_t *staging[kSlots] = {};
     const void *staging_view[kSlots] = {};   // the pinned slots' device addresses
     hipEvent_t done[kSlots] = {};
@@ -70,14 +76,13 @@ std::map<int, std::vector<BatchCtx *>> g_free;
 int init_ctx(BatchCtx *c, int device)
 {
     c->device = device;
-    if (hipMalloc(&c->dev_table, kTableBytes) != hipSuccess)
-        return AES_ENOMEM;
     for (int i = 0; i < kSlots; ++i) {
         // Coherent (fine-grained): the upload kernel reads the slot, and a
         // reused slot must never be served from a line cached by an earlier
         // launch.
         if (hipHostMalloc(reinterpret_cast<void **>(&c->staging[i]), kTableBytes, hipHostMallocCoherent) !=
-            hipSuccess)
+                hipSuccess ||
+            hipMalloc(&c->dev_table[i], kTableBytes) != hipSuccess)
             return AES_ENOMEM;
         void *view = nullptr;
         if (hipHostGetDevicePointer(&view, c->staging[i], 0) != hipSuccess || !view)
@@ -132,9 +137,9 @@ int build_graph(BatchCtx *c, int s, int grid, int bpl)
     if (hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal) != hipSuccess) {
         rc = AES_EDEVICE;
     } else {
-        int lrc = launch_upload(c->staging_view[s], c->dev_table, kTableBytes / 16, cap);
+        int lrc = launch_upload(c->staging_view[s], c->dev_table[s], kTableBytes / 16, cap);
         if (lrc == AES_OK)
-            lrc = launch_ctr_batch(c->dev_table, grid, 1024, bpl, cap);
+            lrc = launch_ctr_batch(c->dev_table[s], grid, 1024, bpl, cap);
         hipGraph_t g = nullptr;
         if (hipStreamEndCapture(cap, &g) != hipSuccess || lrc != AES_OK || !g) {
             rc = lrc != AES_OK ? lrc : AES_EDEVICE;
@@ -321,16 +326,17 @@ int submit_slot(BatchCtx *c, int slot, size_t bytes, hipStream_t st, int grid, i
             if ((rc = build_graph(c, slot, grid, bpl)) != AES_OK)
                 return rc;
         }
-        if (set_upload_node(sg.exec, sg.upload_node, c->staging_view[slot], c->dev_table, quads) != hipSuccess ||
+        if (set_upload_node(sg.exec, sg.upload_node, c->staging_view[slot], c->dev_table[slot], quads) != hipSuccess ||
             hipGraphLaunch(sg.exec, st) != hipSuccess) {
             note_device_error(hipGetLastError());
             return AES_EDEVICE;
         }
     } else {
-        if ((rc = launch_upload(c->staging_view[slot], c->dev_table, quads, st)) != AES_OK)
+        if ((rc = launch_upload(c->staging_view[slot], c->dev_table[slot], quads, st)) != AES_OK)
             return rc;
-        rc = quad ? launch_ctr_quad_table(c->dev_table, *reinterpret_cast<const BatchHeader *>(c->staging[slot]), st)
-                  : launch_ctr_batch(c->dev_table, grid, 1024, bpl, st);
+        void *table = c->dev_table[slot];
+        rc = quad ? launch_ctr_quad_table(table, *reinterpret_cast<const BatchHeader *>(c->staging[slot]), st)
+                  : launch_ctr_batch(table, grid, 1024, bpl, st);
         if (rc != AES_OK)
             return rc;
     }
