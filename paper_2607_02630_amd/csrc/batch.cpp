@@ -313,12 +313,13 @@ int take_slot(BatchCtx *c, int *slot)
     return AES_OK;
 }
 
-// Uploads the first `bytes` of staging slot `slot` into the device table and
+// Uploads the first `bytes` of staging slot `slot` into its device table and
 // launches the batch kernel on st, as two plain launches or through the slot's
 // captured graph of them, then marks the slot busy until that work finishes.
 int submit_slot(BatchCtx *c, int slot, size_t bytes, hipStream_t st, int grid, int bpl, bool use_graph, bool quad)
 {
-    int rc;
+    int rc = AES_OK;
+    void *table = c->dev_table[slot];
     const uint32_t quads = static_cast<uint32_t>((bytes + 15) / 16);
     if (use_graph) {
         SlotGraph &sg = c->g[slot];
@@ -326,26 +327,24 @@ int submit_slot(BatchCtx *c, int slot, size_t bytes, hipStream_t st, int grid, i
             if ((rc = build_graph(c, slot, grid, bpl)) != AES_OK)
                 return rc;
         }
-        if (set_upload_node(sg.exec, sg.upload_node, c->staging_view[slot], c->dev_table[slot], quads) != hipSuccess ||
+        if (set_upload_node(sg.exec, sg.upload_node, c->staging_view[slot], table, quads) != hipSuccess ||
             hipGraphLaunch(sg.exec, st) != hipSuccess) {
             note_device_error(hipGetLastError());
-            return AES_EDEVICE;
+            rc = AES_EDEVICE;
         }
-    } else {
-        if ((rc = launch_upload(c->staging_view[slot], c->dev_table[slot], quads, st)) != AES_OK)
-            return rc;
-        void *table = c->dev_table[slot];
+    } else if ((rc = launch_upload(c->staging_view[slot], table, quads, st)) == AES_OK) {
         rc = quad ? launch_ctr_quad_table(table, *reinterpret_cast<const BatchHeader *>(c->staging[slot]), st)
                   : launch_ctr_batch(table, grid, 1024, bpl, st);
-        if (rc != AES_OK)
-            return rc;
     }
+    // Behind a launch that failed too: the upload ahead of it may be queued, and
+    // the slot must not be rewritten before that has ended.
     if (hipEventRecord(c->done[slot], st) != hipSuccess) {
         note_device_error(hipGetLastError());
+        (void)hipStreamSynchronize(st);
         return AES_EDEVICE;
     }
     c->used[slot] = true;
-    return AES_OK;
+    return rc;
 }
 
 }  // namespace

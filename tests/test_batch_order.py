@@ -12,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "..", "paper_2607_02630_amd", "csrc")
 
 
-@pytest.mark.parametrize("scenario", ["handles"])
+@pytest.mark.parametrize("scenario", ["handles", "failures"])
 def test_uploads_wait_for_every_reader_of_the_table(tmp_path, scenario):
     exe = tmp_path / "batch_order_test"
     subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-pthread", "-I", os.path.join(HERE, "cpp", "fake_hip"), "-I", CSRC,
