@@ -241,8 +241,9 @@ struct SmallBatchArgs {
 };
 static_assert(sizeof(SmallBatchArgs) <= 4096, "kernel arguments are limited to 4 KiB");
 
-// grid: workgroups of the argument-path kernel's own size (256 threads).
-int launch_ctr_batch_small(const SmallBatchArgs &args, int grid, int bpl, hipStream_t st);
+// grid: workgroups of the argument-path kernel's own size (256 threads); shifted:
+// tiles counted by request_tiles, not from the requests' starts.
+int launch_ctr_batch_small(const SmallBatchArgs &args, int grid, int bpl, bool shifted, hipStream_t st);
 
 // Four or two lanes per block (ctr_quad.hip, ctr_pair.hip), a workgroup per tile
 // of this many blocks from a request's start; pairs need at least one tile.

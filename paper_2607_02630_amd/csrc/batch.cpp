@@ -237,6 +237,23 @@ bool quad_table(const BatchDesc *descs, size_t n, int grid)
     return tiles <= 2 * static_cast<uint64_t>(grid);
 }
 
+// How the tiles of a small batch are cut for `waves` waves (run_tile): by position,
+// where a request starts at ctr0 mod 64 and may need one tile more, or from its
+// start, where every step takes 3 to 8% longer.  The tiles more matter when they
+// make one more round of all waves.  us per call, by position and from the start,
+// requests from counter 1: one of 4 MiB (2049 or 2048 tiles, 2048 waves) 9.5 and
+// 7.7, four of 1 MiB 11.4 and 9.3, eight of 8 MiB (two rounds) 74.0 and 67.9.  Not
+// so among thirteen rounds, four where tiles have over 256 blocks (eight requests
+// of 32 MiB 246 and 259), nor for one or two such tiles, which a workgroup's oldest
+// wave takes while the others still work (one of 32 MiB 26.8 and 28.7, two of 16
+// MiB 31.9 and 33.8).
+bool shifted_tiles(uint64_t plain, uint64_t shifted, uint64_t waves, uint32_t tile_blocks)
+{
+    const uint64_t rounds = (plain + waves - 1) / waves;
+    const bool large = tile_blocks > 256;
+    return (shifted + waves - 1) / waves == rounds || rounds >= (large ? 4 : 13) || (large && shifted - plain <= 2);
+}
+
 // A batch of at most kSmallBatch requests goes in the kernel's argument block
 // (no staging slot, no upload), to one of three kernels whose grid it sizes.
 // Where four lanes per block make at most two workgroups per CU of the table
@@ -256,14 +273,18 @@ int launch_small(hipStream_t st, const LaunchSpec &spec, uint32_t tile_blocks, i
 {
     SmallBatchArgs args{};
     const uint64_t cap = 2 * static_cast<uint64_t>(grid);
-    uint64_t quads = 0, pairs = 0;
+    uint64_t quads = 0, pairs = 0, plain = 0, shifted = 0;
     for (size_t i = 0; i < spec.n; ++i) {
-        quads += plain_tiles(spec.descs[i].len, kQuadTileBlocks);
-        pairs += plain_tiles(spec.descs[i].len, kPairTileBlocks);
+        const BatchDesc &d = spec.descs[i];
+        quads += plain_tiles(d.len, kQuadTileBlocks);
+        pairs += plain_tiles(d.len, kPairTileBlocks);
+        plain += plain_tiles(d.len, tile_blocks);
+        shifted += request_tiles(d.len, d.ctr0, tile_blocks);
     }
     const bool quad = quads <= cap, pair = !quad && pairs <= static_cast<uint64_t>(grid);
     if (quad || pair)
         tile_blocks = quad ? kQuadTileBlocks : kPairTileBlocks;
+    const bool shift = !quad && !pair && shifted_tiles(plain, shifted, 4 * cap, tile_blocks);
     uint64_t tiles = 0;
     for (size_t i = 0; i < spec.n; ++i) {
         const BatchDesc &d = spec.descs[i];
@@ -284,7 +305,7 @@ int launch_small(hipStream_t st, const LaunchSpec &spec, uint32_t tile_blocks, i
                     r.install = spec.installs[j].slot;
         }
         r.tile0 = static_cast<uint32_t>(tiles);
-        tiles += quad || pair ? plain_tiles(d.len, tile_blocks) : request_tiles(d.len, d.ctr0, tile_blocks);
+        tiles += shift ? request_tiles(d.len, d.ctr0, tile_blocks) : plain_tiles(d.len, tile_blocks);
         if (tiles > 0x7fffffffu)
             return AES_ERANGE;
     }
@@ -304,7 +325,7 @@ int launch_small(hipStream_t st, const LaunchSpec &spec, uint32_t tile_blocks, i
         return launch_ctr_pair_batch(args, st);
     const uint64_t want = (tiles + 3) / 4;
     const int small_grid = static_cast<int>(std::max<uint64_t>(1, std::min(want, cap)));
-    return launch_ctr_batch_small(args, small_grid, bpl, st);
+    return launch_ctr_batch_small(args, small_grid, bpl, shift, st);
 }
 
 // Takes the context's next staging slot once its last launch has finished.

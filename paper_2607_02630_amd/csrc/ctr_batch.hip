@@ -41,7 +41,7 @@ typedef __attribute__((address_space(4))) const uint32_t c_u32;
 // loads) with round keys rk (wave-uniform, read from the launch's inline keys
 // or from a slot of the resident key table): the request's key material and
 // pointers, then the tile's blocks.
-template <int LAYOUT, int BPL, class Rec>
+template <int LAYOUT, int BPL, bool SHIFTED, class Rec>
 __device__ __forceinline__ void request_tile(const TTable<LAYOUT> &tt, const Rec &R, const uint32_t (&rk)[60],
                                              uint32_t t, uint32_t tile_blocks, uint32_t lane)
 {
@@ -59,7 +59,7 @@ __device__ __forceinline__ void request_tile(const TTable<LAYOUT> &tt, const Rec
 #pragma unroll
     for (int i = 0; i < 60; ++i)
         a.rk[i] = i < 44 || nrk > 44 ? rk[i] : 0;
-    const uint64_t positions = message_shift(a.ctr0) + ((a.len + 15) >> 4);
+    const uint64_t positions = (SHIFTED ? message_shift(a.ctr0) : 0) + ((a.len + 15) >> 4);
     const uint64_t p0 = static_cast<uint64_t>(t - R.tile0) * tile_blocks;
     const uint64_t p1 = p0 + tile_blocks < positions ? p0 + tile_blocks : positions;
     // rotr(rk, 8) of rounds 2..Nr-1 for the two-table fold (the four-table
@@ -70,9 +70,9 @@ __device__ __forceinline__ void request_tile(const TTable<LAYOUT> &tt, const Rec
         for (int i = 8; i < 56; ++i) krot[i] = rotr8(a.rk[i]);
     }
     if (nr == 10)
-        run_tile<10, LAYOUT, BPL>(tt, a, krot, p0, p1, lane);
+        run_tile<10, LAYOUT, BPL, SHIFTED>(tt, a, krot, p0, p1, lane);
     else
-        run_tile<14, LAYOUT, BPL>(tt, a, krot, p0, p1, lane);
+        run_tile<14, LAYOUT, BPL, SHIFTED>(tt, a, krot, p0, p1, lane);
 }
 
 // Writes the round keys of key record `src` (64 words) into slot `slot` of
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(kBatchWG) void ctr_batch_kernel(const uint8_t *__re
 #pragma unroll
             for (int i = 0; i < 60; ++i) rk[i] = p[i];
         }
-        request_tile<kBatchLayout, BPL>(tt, R, rk, t, tile_blocks, lane);
+        request_tile<kBatchLayout, BPL, true>(tt, R, rk, t, tile_blocks, lane);
         if (mine)
             k = next_own();
     }
@@ -215,7 +215,8 @@ __global__ __launch_bounds__(kUploadWG) void upload_kernel(const u32x4 *__restri
 // host-to-device copy adds about 20 us to a small batch's latency).  Tiles
 // are assigned statically, wave w taking tiles w, w + W, w + 2W, ... (W
 // waves, numbered as in ctr_batch_kernel), so no work counter is needed.
-template <int BPL>
+// SHIFTED: how tiles are cut (see run_tile and launch_small).
+template <int BPL, bool SHIFTED>
 __global__ __launch_bounds__(kSmallWG) void ctr_batch_small_kernel(const SmallBatchArgs args)
 {
     __shared__ uint32_t lds[layout_lds_words(kSmallLayout)];
@@ -254,7 +255,7 @@ __global__ __launch_bounds__(kSmallWG) void ctr_batch_small_kernel(const SmallBa
 #pragma unroll
             for (int i = 0; i < 60; ++i) rk[i] = R.rk[i];
         }
-        request_tile<kSmallLayout, BPL>(tt, R, rk, t, args.tile_blocks, lane);
+        request_tile<kSmallLayout, BPL, SHIFTED>(tt, R, rk, t, args.tile_blocks, lane);
     }
 }
 
@@ -304,16 +305,14 @@ int launch_ctr_batch(const void *dev_table, int grid, int wg, int bpl, hipStream
     return launch_status();
 }
 
-int launch_ctr_batch_small(const SmallBatchArgs &args, int grid, int bpl, hipStream_t st)
+int launch_ctr_batch_small(const SmallBatchArgs &args, int grid, int bpl, bool shifted, hipStream_t st)
 {
-    if (grid <= 0 || grid > kMaxBatchGrid || args.n > kSmallBatch)
+    if (grid <= 0 || grid > kMaxBatchGrid || args.n > kSmallBatch || (bpl != 1 && bpl != 2))
         return AES_EINVAL;
     (void)hipGetLastError();   // not ours: left by earlier calls
-    switch (bpl) {
-    case 1: hipLaunchKernelGGL(ctr_batch_small_kernel<1>, dim3(grid), dim3(kSmallWG), 0, st, args); break;
-    case 2: hipLaunchKernelGGL(ctr_batch_small_kernel<2>, dim3(grid), dim3(kSmallWG), 0, st, args); break;
-    default: return AES_EINVAL;
-    }
+    auto kernel = shifted ? (bpl == 1 ? ctr_batch_small_kernel<1, true> : ctr_batch_small_kernel<2, true>)
+                          : (bpl == 1 ? ctr_batch_small_kernel<1, false> : ctr_batch_small_kernel<2, false>);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kSmallWG), 0, st, args);
     return launch_status();
 }
 

@@ -117,12 +117,17 @@ __device__ __forceinline__ void span_step(const TTable<LAYOUT> &tt, const CtrArg
 // Positions [p0, p1) of message a, p0 a multiple of 64 and p1 - p0 below 2^31,
 // N x 64 of them per step; positions outside the message are left out.  krot:
 // rotr(rk, 8) for the two-table layouts.
-template <int NR, int LAYOUT, int N>
+//
+// SHIFTED: positions are as above.  Otherwise position j is block j: a tile then
+// holds as many blocks as positions, which counts where a launch has just enough
+// waves for its tiles, but the 64 counters of a step may span two groups, so their
+// constants are chosen per lane (8 more v_readlane and 4 selects per 64 blocks).
+template <int NR, int LAYOUT, int N, bool SHIFTED = true>
 __device__ __forceinline__ void run_tile(const TTable<LAYOUT> &tt, const CtrArgs &a, const uint32_t *krot, uint64_t p0,
                                          uint64_t p1, uint32_t lane)
 {
     static_assert(N == 1 || N == 2, "steps of 64 or 128 blocks");
-    const uint32_t shift = message_shift(a.ctr0);
+    const uint32_t shift = SHIFTED ? message_shift(a.ctr0) : 0;
     const uint32_t n = static_cast<uint32_t>(p1 - p0);
     const uint32_t tail = static_cast<uint32_t>(a.len & 15);
     const Span sp = message_span(a, shift, p0, p1);
@@ -136,21 +141,38 @@ __device__ __forceinline__ void run_tile(const TTable<LAYOUT> &tt, const CtrArgs
         if (64u * k < n)
             lane_consts(tt, a, first + 64 * k + lane, L[k]);
     uint32_t Gv[4];
-    uint32_t window = ~0u;    // the 64 groups whose constants Gv holds, counted from p0's
+    uint32_t window = SHIFTED ? ~0u : 0u - 64u;    // the 64 groups whose constants Gv holds, counted from p0's:
+                                                   // their number / 64, or the first of them
     for (uint32_t q = 0; q < n;) {
 #pragma unroll
         for (int k = 0; k < 4; k += N) {
             uint32_t G[N][4];
 #pragma unroll
             for (int b = 0; b < N; ++b) {
-                const uint32_t g = ((first & 255u) + q + 64 * b) >> 8;
-                if ((g >> 6) != window) {
-                    window = g >> 6;
-                    group_consts_lds(tt, a, ((first >> 8) + (window << 6) + lane) & 0xffffffu, Gv);
-                }
+                const uint32_t c0 = (first & 255u) + q + 64 * b, g = c0 >> 8;
+                if constexpr (SHIFTED) {
+                    if ((g >> 6) != window) {
+                        window = g >> 6;
+                        group_consts_lds(tt, a, ((first >> 8) + (window << 6) + lane) & 0xffffffu, Gv);
+                    }
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    G[b][c] = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(Gv[c]), g & 63));
+                    for (int c = 0; c < 4; ++c)
+                        G[b][c] = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(Gv[c]), g & 63));
+                } else {
+                    const uint32_t g1 = (c0 + 63) >> 8;
+                    if (g1 - window > 63) {
+                        window = g;
+                        group_consts_lds(tt, a, ((first >> 8) + window + lane) & 0xffffffu, Gv);
+                    }
+                    const bool next = (c0 & 255u) + lane > 255u;
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const int v = static_cast<int>(Gv[c]);
+                        const int lo = __builtin_amdgcn_readlane(v, g - window);
+                        const int hi = __builtin_amdgcn_readlane(v, g1 - window);
+                        G[b][c] = static_cast<uint32_t>(next ? hi : lo);
+                    }
+                }
             }
             span_step<NR, LAYOUT, N>(tt, a, krot, sp, q, lane, &L[k], G, part);
             q += 64 * N;

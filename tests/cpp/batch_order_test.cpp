@@ -5,6 +5,10 @@
 // the table's upload is queued.  Every upload has to be ordered behind all work
 // that reads or writes the table, and a pinned slot is rewritten only when the
 // upload from it has ended.
+//
+// "routes" instead reads batches "requests bytes ctr0 tile_bytes blocks_per_lane
+// grid use_graph" from stdin and prints the launch of each: "kernel tiles
+// tile_blocks workgroups blocks_per_lane".
 #include <stdio.h>
 #include <stdlib.h>
 
@@ -30,7 +34,7 @@ std::vector<Op> g_ops;
 std::set<int> g_tail[4];        // per queue: what its next operation waits for
 std::set<int> g_host;           // operations the host has waited for
 int g_queue = 0;                // the queue that stream handles stand for now
-bool g_capturing = false, g_fail_kernel = false;
+bool g_capturing = false, g_fail_kernel = false, g_routes = false;
 Graph g_captured;
 int g_races = 0;
 
@@ -122,19 +126,36 @@ hipError_t set_upload_node(hipGraphExec_t x, hipGraphNode_t, const void *src, vo
 {
     return *static_cast<Graph *>(x) = Graph{src, dst}, hipSuccess;
 }
-static int kernel(const void *table)
+static int kernel(const char *name, const void *table, int grid, int bpl)
 {
     if (g_fail_kernel)
         return AES_EDEVICE;
-    if (!g_capturing)
-        enqueue(table, nullptr);
+    if (g_capturing)
+        return AES_OK;
+    enqueue(table, nullptr);
+    // The upload has not run: the table as staged.
+    const BatchHeader *h = reinterpret_cast<const BatchHeader *>(g_ops[g_ops.size() - 2].src);
+    if (g_routes)
+        printf("%s %u %u %d %d\n", name, h->total_tiles, h->tile_blocks, grid, bpl);
     return AES_OK;
 }
-int launch_ctr_batch(const void *table, int, int, int, hipStream_t) { return kernel(table); }
-int launch_ctr_quad_table(const void *table, const BatchHeader &, hipStream_t) { return kernel(table); }
-int launch_ctr_batch_small(const SmallBatchArgs &, int, int, hipStream_t) { return AES_OK; }
-int launch_ctr_quad_batch(const SmallBatchArgs &, hipStream_t) { return AES_OK; }
-int launch_ctr_pair_batch(const SmallBatchArgs &, hipStream_t) { return AES_OK; }
+static int small(const char *name, const SmallBatchArgs &a, int grid, int bpl)
+{
+    if (g_routes)
+        printf("%s %u %u %d %d\n", name, a.total_tiles, a.tile_blocks, grid, bpl);
+    return AES_OK;
+}
+int launch_ctr_batch(const void *table, int grid, int, int bpl, hipStream_t) { return kernel("table", table, grid, bpl); }
+int launch_ctr_quad_table(const void *table, const BatchHeader &h, hipStream_t)
+{
+    return kernel("quad_table", table, static_cast<int>(h.total_tiles), 0);
+}
+int launch_ctr_batch_small(const SmallBatchArgs &a, int grid, int bpl, bool shifted, hipStream_t)
+{
+    return small(shifted ? "small" : "small_plain", a, grid, bpl);
+}
+int launch_ctr_quad_batch(const SmallBatchArgs &a, hipStream_t) { return small("quad", a, a.total_tiles, 0); }
+int launch_ctr_pair_batch(const SmallBatchArgs &a, hipStream_t) { return small("pair", a, a.total_tiles, 0); }
 void note_device_error(hipError_t) {}
 int device_info(DeviceInfo *out) { return *out = DeviceInfo{0, 256, 163840}, AES_OK; }
 int check_sched(const aes_sched_t *) { return AES_OK; }
@@ -142,13 +163,39 @@ int check_buffers(const void *, const void *, uint64_t) { return AES_OK; }
 
 }  // namespace aesctr
 
+static int routes(const aes_sched_t &s)
+{
+    g_routes = true;
+    unsigned long long n, len;
+    unsigned ctr0;
+    aes_batch_cfg_t cfg{};
+    while (scanf("%llu %llu %u %d %d %d %d", &n, &len, &ctr0, &cfg.tile_bytes, &cfg.blocks_per_lane, &cfg.grid,
+                 &cfg.use_graph) == 7) {
+        std::vector<aes_ctr_desc_t> d(n);
+        for (aes_ctr_desc_t &r : d) {
+            r = aes_ctr_desc_t{};
+            r.in = r.out = reinterpret_cast<void *>(uintptr_t(1) << 40);
+            r.len = len;
+            r.ctr0 = ctr0;
+            r.sched = &s;
+        }
+        if (aes_ctr_crypt_batch_cfg(d.data(), d.size(), &cfg, nullptr) != AES_OK)
+            return 1;
+        if (cfg.use_graph && n > 8)
+            printf("graph 0 0 0 0\n");
+    }
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
-    const bool fail = argc > 1 && argv[1][0] == 'f';    // "failures" or "handles"
+    const bool fail = argc > 1 && argv[1][0] == 'f';    // "failures", "handles" or "routes"
     const uint8_t key[16] = {};
     aes_sched_t s;
     if (aes_expand_key(key, 128, &s) != AES_OK)
         return 1;
+    if (argc > 1 && argv[1][0] == 'r')
+        return routes(s);
     uintptr_t handle = 2;    // a context of its own per scenario
     for (int use_graph = 0; use_graph < (fail ? 1 : 2); ++use_graph)    // (a failed graph launch queues nothing)
         for (uint64_t len : {uint64_t(100), uint64_t(1) << 20}) {

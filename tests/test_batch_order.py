@@ -12,12 +12,37 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "..", "paper_2607_02630_amd", "csrc")
 
 
-@pytest.mark.parametrize("scenario", ["handles", "failures"])
-def test_uploads_wait_for_every_reader_of_the_table(tmp_path, scenario):
-    exe = tmp_path / "batch_order_test"
+@pytest.fixture(scope="module")
+def exe(tmp_path_factory):
+    out = tmp_path_factory.mktemp("batch") / "batch_order_test"
     subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-pthread", "-I", os.path.join(HERE, "cpp", "fake_hip"), "-I", CSRC,
-                    "-o", str(exe), os.path.join(HERE, "cpp", "batch_order_test.cpp"),
+                    "-o", str(out), os.path.join(HERE, "cpp", "batch_order_test.cpp"),
                     *(os.path.join(CSRC, f) for f in ("batch.cpp", "host_pool.cpp", "keys.cpp", "tune.cpp")), "-ldl"],
                    check=True)
-    r = subprocess.run([str(exe), scenario], capture_output=True, text=True, timeout=60)
+    return str(out)
+
+
+@pytest.mark.parametrize("scenario", ["handles", "failures"])
+def test_uploads_wait_for_every_reader_of_the_table(exe, scenario):
+    r = subprocess.run([exe, scenario], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and "batch order ok" in r.stdout, r.stdout + r.stderr
+
+
+def routes(exe, batches):
+    """[(requests, bytes, ctr0, tile_bytes, blocks_per_lane, grid, use_graph)] -> [(kernel, tiles, tile_blocks,
+    workgroups, blocks_per_lane)]."""
+    r = subprocess.run([exe, "routes"], input="".join(" ".join(map(str, b)) + "\n" for b in batches), capture_output=True,
+                       text=True, timeout=60, check=True, env=dict(os.environ, AESCTR_TUNE_CACHE=""))
+    got = [line.split() for line in r.stdout.splitlines()]
+    assert len(got) == len(batches), r.stdout
+    return [(g[0], *map(int, g[1:])) for g in got]
+
+
+@pytest.mark.parametrize("n,size,tile", [(1, 4 << 20, 0), (4, 1 << 20, 0), (8, 512 << 10, 0), (8, 1 << 20, 0), (2, 4 << 20, 0),
+                                         (1, 8 << 20, 0), (8, 8 << 20, 0), (4, 1 << 20, 2048)])
+def test_a_start_counter_adds_no_round_of_tiles(exe, n, size, tile):
+    """Requests that fill all waves of the small batch's kernel exactly need no further tile for a
+    start counter within 64 counters: 2048 waves on 256 CUs."""
+    even, odd = routes(exe, [(n, size, 0, tile, 0, 0, 0), (n, size, 1, tile, 0, 0, 0)])
+    assert even[0] == "small" and even[1] % 2048 == 0, even
+    assert odd[0] == "small_plain" and odd[1:3] == even[1:3], odd
