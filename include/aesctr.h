@@ -156,20 +156,21 @@ int aes_ctr_crypt_cfg(const aes_sched_t *sched, const uint8_t nonce[12], uint32_
                       const aes_launch_cfg_t *cfg, void *stream);
 
 /* The launch shape aes_ctr_crypt_cfg would use for a len-byte message with
- * this key size and cfg (NULL = defaults): the default shape, or the tune
- * cache's entry for the same floor(log2(len)) where it has one (of the T-table
- * kernel's only if its grid takes the message in as many chunks as the size it
- * was tuned at).  Non-zero fields of cfg that name another shape than that change
- * one of the T-table kernel's own for that size instead (its entry, or 1 x 256, 1 x 512 or
- * 2 x 512 blocks per lane and threads up to 8 MiB on 256 CUs, 4 x 512 from 16),
- * so what they name does not depend on which kernel the default call runs.  The
- * grid is clamped to the work.  For a small message that runs with four or two
- * lanes per block (see aes_launch_cfg_t) this is the shape that the T-table kernel
- * would take, which the call runs when the shape is handed back to it.  All fields of *out are set (variant 1,
- * 2 or 3, never AUTO; lds_copies and lds_tables 0 for the kernels without
- * T-tables).  Host only; it
- * needs the current device's CU count.  Errors: AES_EINVAL (null out, key
- * size not 128/256, bad cfg), AES_EDEVICE. */
+ * this key size and cfg (NULL = defaults), in buffers at multiples of 16 bytes
+ * (at others only the default from 21 to 24 MiB on 256 CUs differs): the
+ * default shape, or the tune cache's entry for the same floor(log2(len)) where
+ * it has one (of the T-table kernel's only if its grid takes the message in as
+ * many chunks as the size it was tuned at).  Non-zero fields of cfg that name
+ * another shape than that change one of the T-table kernel's own for that size
+ * instead (its entry, or 1 x 256, 1 x 512 or 2 x 512 blocks per lane and threads
+ * up to 16 MiB on 256 CUs and 4 x 512 from there), so what they name does not
+ * depend on which kernel the default call runs.  The grid is clamped to the
+ * work.  For a small message that runs with four or two lanes per block (see
+ * aes_launch_cfg_t) this is the shape that the T-table kernel would take, which
+ * the call runs when the shape is handed back to it.  All fields of *out are set
+ * (variant 1, 2 or 3, never AUTO; lds_copies and lds_tables 0 for the kernels
+ * without T-tables).  Host only; it needs the current device's CU count.
+ * Errors: AES_EINVAL (null out, key size not 128/256, bad cfg), AES_EDEVICE. */
 int aes_ctr_launch_shape(int key_bits, size_t len, const aes_launch_cfg_t *cfg, aes_launch_cfg_t *out);
 
 /* ---------------------------------------------------------------------- */

@@ -311,6 +311,6 @@ size_t finish_stage(uint8_t *buf, size_t n, uint32_t tile_blocks, int grid, bool
 void release_batch_stream(int device, hipStream_t st);
 
 // Defaults before tuning, per variant and size.
-Shape default_shape(int variant, int key_bits, uint64_t len, const DeviceInfo &di);
+Shape default_shape(int variant, int key_bits, uint64_t len, bool aligned, const DeviceInfo &di);
 
 }  // namespace aesctr

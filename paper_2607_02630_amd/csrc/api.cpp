@@ -155,6 +155,24 @@ Shape explicit_base(int key_bits, uint64_t len, const DeviceInfo &di)
     return sh;
 }
 
+// Whether a message of 16 to 32 MiB on 256 CUs runs in steps of a chunk per CU
+// rather than in shared tiles, whose time grows with the length: where the last
+// step is nearly full.  At 23 MiB, steps against tiles, AES-128 and AES-256: 17.9
+// us against 18.6 and 23.7 against 25.0; with a partial block, which one thread
+// takes behind its chunk, 18.8 against 18.7 and 24.1 against 25.1; at an odd
+// address, where a wave's 1 KiB of payload touches one line more, 20.1 against 18.9
+// and 25.0 against 24.9.  Third steps: from three quarters (AES-256: two thirds, 21.5
+// MiB, 23.3 against 22.9).  Fourth steps: a full one (32 MiB 23.5 against 23.5);
+// below that the tiles (31.5 MiB 23.4 against 23.4, with a partial block 24.2 against
+// 23.5).
+bool steps_fit(uint64_t len, uint64_t chunks, uint64_t cus, int key_bits, bool aligned)
+{
+    const uint64_t done = (chunks - 1) / cus, last = chunks - done * cus;
+    if (done != 2)
+        return done < 2 || last == cus;
+    return aligned && (key_bits == 256 ? 3 * last >= 2 * cus : len % 16 == 0 && 4 * last >= 3 * cus);
+}
+
 // Whether cfg names any part of the launch shape.
 bool names_shape(const aes_launch_cfg_t *cfg)
 {
@@ -173,7 +191,7 @@ bool other_shape(const aes_launch_cfg_t &cfg, const Shape &def)
 
 }  // namespace
 
-Shape default_shape(int variant, int key_bits, uint64_t len, const DeviceInfo &di)
+Shape default_shape(int variant, int key_bits, uint64_t len, bool aligned, const DeviceInfo &di)
 {
     Shape sh{};
     sh.variant = variant == AES_VARIANT_AUTO ? AES_VARIANT_TTABLE : variant;
@@ -207,13 +225,14 @@ Shape default_shape(int variant, int key_bits, uint64_t len, const DeviceInfo &d
         // Where every workgroup has one chunk (up to 1024), and with one block
         // per lane, rounds 1-2 of the first chunk run in full (first-chunk mode
         // 2: no group constants, no second barrier).
-        // From 16 MiB on that shape takes steps of a chunk per CU (32 KiB x
-        // CUs), so it stays only where chunks are a whole number per CU, up to
-        // 32 MiB; else one persistent workgroup per CU (ctr_bulk.hip), whose
-        // waves share 4 KiB tiles.  AES-128: 16 MiB 12.9 us (bulk 13.5), 16 MiB +
-        // 100 bytes 17.6 (13.6), 24 MiB 18.0 (19.1), 32 MiB 23.0 (23.2), 48 MiB
-        // 35.2 (31.1), 96.3 MiB 70.6 (60.4), 256 MiB 167 (153); AES-256: 16 MiB
-        // 17.3 (17.7), 32 MiB 30.6 (31.6), 48 MiB 47.6 (42.7), 256 MiB 230 (208).
+        // From 16 MiB on that shape takes steps of a chunk per CU (32 KiB x CUs), so it
+        // stays only up to 32 MiB and where its last step is nearly full (steps_fit);
+        // else one persistent workgroup per CU (ctr_bulk.hip), whose waves share 4 KiB
+        // tiles.  AES-128: 16 MiB 13.0 us (bulk 13.4), 16 MiB + 100 bytes 17.0 (13.6),
+        // 22 MiB 18.0 (17.7), 23 MiB 18.2 (18.5), 24 MiB 18.4 (19.0), 25 MiB 21.8
+        // (19.9), 32 MiB 23.5 (23.5), 48 MiB 35.2 (31.1), 96.3 MiB 70.6 (60.4), 256 MiB
+        // 167 (153); AES-256: 16 MiB 17.1 (17.7), 21 MiB 23.3 (22.6), 22 MiB 23.4 (24.1),
+        // 24 MiB 24.3 (25.4), 32 MiB 31.0 (31.1), 48 MiB 47.6 (42.7), 256 MiB 230 (208).
         sh.grid = di.num_cus;
         sh.copies = 32;
         sh.tables = 2;
@@ -232,7 +251,7 @@ Shape default_shape(int variant, int key_bits, uint64_t len, const DeviceInfo &d
             sh.bpl = 2;
             sh.grid = (per_cu <= 3072 ? 2 : 4) * di.num_cus;
             sh.wave_groups = kFirstPerWave;
-        } else if (per_cu <= 8192 && chunks % cus == 0) {
+        } else if (per_cu <= 8192 && steps_fit(len, chunks, cus, key_bits, aligned)) {
             sh.bpl = 4;
             sh.grid = 4 * di.num_cus;
         } else {
@@ -329,10 +348,12 @@ int check_cfg(const aes_launch_cfg_t *cfg, int *variant)
 }
 
 // The launch shape for len bytes: the default (or tuned) shape, overridden
-// by the non-zero fields of cfg, with the grid clamped to the work.
-Shape resolve_shape(int variant, int key_bits, uint64_t len, const aes_launch_cfg_t *cfg, const DeviceInfo &di)
+// by the non-zero fields of cfg, with the grid clamped to the work.  aligned: in
+// and out are at multiples of 16 bytes.
+Shape resolve_shape(int variant, int key_bits, uint64_t len, bool aligned, const aes_launch_cfg_t *cfg,
+                    const DeviceInfo &di)
 {
-    Shape sh = default_shape(variant, key_bits, len, di);
+    Shape sh = default_shape(variant, key_bits, len, aligned, di);
     if (cfg && sh.variant == AES_VARIANT_TTABLE && other_shape(*cfg, sh))
         sh = explicit_base(key_bits, len, di);
     if (cfg) {
@@ -387,7 +408,7 @@ extern "C" int aes_ctr_launch_shape(int key_bits, size_t len, const aes_launch_c
     DeviceInfo di;
     if ((rc = device_info(&di)) != AES_OK)
         return rc;
-    const Shape sh = resolve_shape(variant, key_bits, len ? len : 1, cfg, di);
+    const Shape sh = resolve_shape(variant, key_bits, len ? len : 1, true, cfg, di);
     *out = aes_launch_cfg_t{};
     out->variant = sh.variant;
     out->blocks_per_lane = sh.bpl;
@@ -422,7 +443,8 @@ extern "C" int aes_ctr_crypt_cfg(const aes_sched_t *sched, const uint8_t nonce[1
     DeviceInfo di;
     if ((rc = device_info(&di)) != AES_OK)
         return rc;
-    const Shape sh = resolve_shape(variant, sched->key_bits, len, cfg, di);
+    const bool aligned = ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
+    const Shape sh = resolve_shape(variant, sched->key_bits, len, aligned, cfg, di);
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (sh.variant == AES_VARIANT_VPERM) {

@@ -1,5 +1,5 @@
 // Reads launch requests "key_bits len variant blocks_per_lane wg_size grid
-// lds_copies lds_tables wave_groups" from stdin and prints for each what
+// lds_copies lds_tables wave_groups address" from stdin and prints for each what
 // aes_ctr_crypt_cfg does with it: "status kernel blocks_per_lane wg grid copies
 // tables mode", the shape as the kernel's launcher gets it.  The launchers are
 // stand-ins that take what the kernels are built for.
@@ -63,9 +63,10 @@ int main()
     unsigned long long len;
     aes_launch_cfg_t c{};
     const uint8_t key[32] = {}, nonce[12] = {};
-    void *buf = reinterpret_cast<void *>(uintptr_t(1) << 40);
-    while (scanf("%d %llu %d %d %d %d %d %d %d", &bits, &len, &c.variant, &c.blocks_per_lane, &c.wg_size, &c.grid,
-                 &c.lds_copies, &c.lds_tables, &c.wave_groups) == 9) {
+    int address;
+    while (scanf("%d %llu %d %d %d %d %d %d %d %d", &bits, &len, &c.variant, &c.blocks_per_lane, &c.wg_size, &c.grid,
+                 &c.lds_copies, &c.lds_tables, &c.wave_groups, &address) == 10) {
+        void *buf = reinterpret_cast<void *>((uintptr_t(1) << 40) + address);
         aes_sched_t s;
         if (aes_expand_key(key, bits, &s) != AES_OK)
             return 1;

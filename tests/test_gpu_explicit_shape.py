@@ -1,5 +1,5 @@
-"""Calls that name a part of the launch shape: output against the CPU oracle, at
-sizes whose default call runs another kernel than the T-table kernel."""
+"""Calls that name a part of the launch shape, or nothing: output against the CPU
+oracle, at sizes near those where the default call changes its kernel."""
 from __future__ import annotations
 
 import numpy as np
@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("bits", [128, 256])
 @pytest.mark.parametrize("per_cu,kw", [(4100, dict(blocks_per_lane=2, wave_groups=2)),
                                        (4100, dict(blocks_per_lane=1, wave_groups=1, grid=64)),
-                                       (8300, dict(wg_size=256)), (8300, dict(lds_copies=64)), (300, dict(grid=1000))])
+                                       (8300, dict(wg_size=256)), (8300, dict(lds_copies=64)), (300, dict(grid=1000)),
+                                       (6128, dict()), (5400, dict())])
 def test_a_part_of_the_shape(bits, per_cu, kw):
     torch = torch_cuda()
     import paper_2607_02630_amd as A

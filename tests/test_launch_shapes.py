@@ -14,7 +14,7 @@ import pytest
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "..", "paper_2607_02630_amd", "csrc")
 SHIPPED = os.path.join(HERE, "..", "paper_2607_02630_amd", "tune_cache.json")
-FIELDS = ("variant", "bpl", "wg", "grid", "copies", "tables", "mode")
+FIELDS = ("variant", "bpl", "wg", "grid", "copies", "tables", "mode", "address")
 MiB = 1 << 20
 
 
@@ -95,3 +95,27 @@ def test_several_lanes_per_block_only_for_callers_who_name_no_shape(exe):
                 rc, got, shape = ask(exe, [(bits, n, kw)])[0]
                 assert (rc, got) == (0, "ttable"), (bits, n, kw, got)
                 assert shape[2] <= kw.get("grid", 256 + 1), (bits, n, kw, shape)
+
+
+# Where the default changes between steps of a chunk per CU ("ttable", 512 threads of 4 blocks) and shared tiles ("bulk"),
+# by how full the last step is: MiB on 256 CUs, for both key sizes.
+STEPS = [(16, "ttable", "ttable"), (16.125, "bulk", "bulk"), (21, "bulk", "bulk"), (21.5, "bulk", "ttable"),
+         (21.875, "bulk", "ttable"), (22.125, "ttable", "ttable"), (23.9375, "ttable", "ttable"), (24, "ttable", "ttable"),
+         (24.125, "bulk", "bulk"), (31.5, "bulk", "bulk"), (32, "ttable", "ttable"), (32.125, "bulk", "bulk"),
+         (40, "bulk", "bulk")]
+
+
+def test_nearly_full_steps_keep_their_shape(exe):
+    for i, bits in enumerate((128, 256)):
+        for m, *kernels in STEPS:
+            rc, kernel, shape = ask(exe, [(bits, int(m * MiB), {})])[0]
+            assert (rc, kernel) == (0, kernels[i]), (bits, m, kernel, shape)
+            assert shape[:2] == ((4, 512) if kernel == "ttable" else (2, 1024)), (bits, m, shape)
+
+
+def test_steps_only_where_their_partial_blocks_and_addresses_cost_less(exe):
+    """At an odd address shared tiles take less; a partial block matters to AES-128 alone."""
+    for bits in (128, 256):
+        assert ask(exe, [(bits, 23 * MiB, dict(address=3))])[0][1] == "bulk"
+    assert ask(exe, [(128, 23 * MiB + 5, {})])[0][1] == "bulk"
+    assert ask(exe, [(256, 23 * MiB + 5, {})])[0][1] == "ttable"
