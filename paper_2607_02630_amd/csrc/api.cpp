@@ -219,8 +219,8 @@ Shape default_shape(int variant, int key_bits, uint64_t len, bool aligned, const
         //   up to 1536  512 x 1, two per CU  4.3 MiB 6.42 (8.30), 6 MiB 6.42 (7.36)
         //   up to 2048  512 x 2, two per CU  6.8 MiB 7.57 (8.23), 8 MiB 7.65 (8.14)
         //   up to 2560  512 x 1, two per CU  8.2 MiB 8.71 (9.29), 9.8 MiB 9.10 (9.51)
-        //   up to 3072  512 x 2, two per CU  11.7 MiB 9.77 (10.48)
-        //   below 4096  512 x 2, four per CU 13.7 MiB 12.92 (13.33)
+        //   below 4096  512 x 2, two per CU  11.7 MiB 9.77 (10.48); four per CU: 13.7
+        //                                    MiB 12.4 (12.7), 16 MiB 12.9 (13.1)
         // and 512 x 4, four per CU, from 16 MiB.  AES-256 has the same order.
         // Where every workgroup has one chunk (up to 1024), and with one block
         // per lane, rounds 1-2 of the first chunk run in full (first-chunk mode
@@ -249,7 +249,7 @@ Shape default_shape(int variant, int key_bits, uint64_t len, bool aligned, const
             sh.wave_groups = kFirstFull;
         } else if (per_cu < 4096) {
             sh.bpl = 2;
-            sh.grid = (per_cu <= 3072 ? 2 : 4) * di.num_cus;
+            sh.grid = 2 * di.num_cus;
             sh.wave_groups = kFirstPerWave;
         } else if (per_cu <= 8192 && steps_fit(len, chunks, cus, key_bits, aligned)) {
             sh.bpl = 4;

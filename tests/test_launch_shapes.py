@@ -113,6 +113,13 @@ def test_nearly_full_steps_keep_their_shape(exe):
             assert shape[:2] == ((4, 512) if kernel == "ttable" else (2, 1024)), (bits, m, shape)
 
 
+def test_two_workgroups_per_cu_below_16_mib(exe):
+    """Two chunks of 512 threads x 2 blocks are resident; more workgroups in the grid fill their tables for one more."""
+    for bits in (128, 256):
+        for n in (11_700_000, 12 * MiB + 16, 13_700_000, 15_900_000):
+            assert ask(exe, [(bits, n, {})])[0] == (0, "ttable", (2, 512, 512, 32, 2, 1)), (bits, n)
+
+
 def test_steps_only_where_their_partial_blocks_and_addresses_cost_less(exe):
     """At an odd address shared tiles take less; a partial block matters to AES-128 alone."""
     for bits in (128, 256):
