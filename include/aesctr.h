@@ -215,14 +215,14 @@ int aes_ctr_crypt_batch(const aes_ctr_desc_t *desc, size_t n, void *stream);
  * multiple of 1024), wg_size, grid, blocks_per_lane; zero = default (tiles
  * sized to the batch, about sixteen per CU within 2-64 KiB; 2 blocks per
  * lane; 1024-thread workgroups, one per CU; a tune cache may override).
- * use_graph: 1 = a captured graph of upload and kernel, 0 = two plain launches;
- * a call without cfg launches plainly, which is the faster, and up to 256
- * requests of at most twice `grid` times 64 blocks then run with four lanes per
- * block, whatever tile_bytes and blocks_per_lane say; batches of at most 8 requests use neither: their kernel
- * has 256-thread workgroups, a wave per tile up to twice `grid` workgroups,
- * and takes tile_bytes and blocks_per_lane from cfg like the table kernel, or,
- * where that holds it all, runs with four lanes per block (workgroups of 64
- * blocks, up to twice `grid` of them) or two (of 256 blocks, up to `grid`). */
+ * use_graph: 1 = a captured graph of upload and kernel, 0 = two plain launches,
+ * as a call without cfg makes them, which is the faster.
+ * Batches of at most 8 requests make one launch, of 256-thread workgroups, a
+ * wave per tile up to twice `grid` workgroups.
+ * Where tile_bytes and blocks_per_lane (and, for more than 8 requests, wg_size and
+ * use_graph) are zero, up to 256 requests may run with four lanes per block, in
+ * 256-thread workgroups of 64 blocks, up to twice `grid` of them, and up to 8
+ * requests with two, in 512-thread workgroups of 256 blocks, up to `grid`. */
 typedef struct {
     int32_t tile_bytes;
     int32_t wg_size;

@@ -226,7 +226,8 @@ constexpr size_t kRecordGrain = 256;
 // table kernel: 9 requests of 0.1-1 KB 10.4 (15.0) and 18.2 (22.4), 64 of them 11.1
 // (15.4) and 20.0 (24.3), 256 of 0.1-4 KB 14.6 (17.1) and 26.2 (29.7), 12 of 20-60
 // KB 11.2 (15.3) and 19.4 (23.0).  Not through a captured graph, whose second node
-// is the table kernel.
+// is the table kernel, nor where the caller names that kernel's tiles, blocks per
+// lane or workgroup size.
 bool quad_table(const BatchDesc *descs, size_t n, int grid)
 {
     if (n > kQuadTableReqs)
@@ -268,8 +269,9 @@ bool shifted_tiles(uint64_t plain, uint64_t shifted, uint64_t waves, uint32_t ti
 // (21.4), in pinned host memory 30.2 (33.4) for one call.  Pairs: one request of 1
 // MiB 4.8 (8.1) and 17.0 (20.2); 8 of 128 KiB 4.8 (9.6) and 16.9 (21.9), in pinned
 // host memory 47.5 (49.7).
-// Returns AES_OK, AES_ERANGE or AES_EDEVICE.
-int launch_small(hipStream_t st, const LaunchSpec &spec, uint32_t tile_blocks, int grid, int bpl)
+// several: whether the first two may take it (not where the caller names the last
+// one's tiles or blocks per lane).  Returns AES_OK, AES_ERANGE or AES_EDEVICE.
+int launch_small(hipStream_t st, const LaunchSpec &spec, uint32_t tile_blocks, int grid, int bpl, bool several)
 {
     SmallBatchArgs args{};
     const uint64_t cap = 2 * static_cast<uint64_t>(grid);
@@ -281,7 +283,8 @@ int launch_small(hipStream_t st, const LaunchSpec &spec, uint32_t tile_blocks, i
         plain += plain_tiles(d.len, tile_blocks);
         shifted += request_tiles(d.len, d.ctr0, tile_blocks);
     }
-    const bool quad = quads <= cap, pair = !quad && pairs <= static_cast<uint64_t>(grid);
+    const bool quad = several && quads <= cap;
+    const bool pair = several && !quad && pairs <= static_cast<uint64_t>(grid);
     if (quad || pair)
         tile_blocks = quad ? kQuadTileBlocks : kPairTileBlocks;
     const bool shift = !quad && !pair && shifted_tiles(plain, shifted, 4 * cap, tile_blocks);
@@ -386,7 +389,7 @@ int launch_spec(int device, hipStream_t st, const LaunchSpec &spec, int tile_byt
         spec.n_install > static_cast<size_t>(kMaxBatch))
         return AES_EINVAL;
     if (allow_small && spec.n <= kSmallBatch)
-        return launch_small(st, spec, tile_blocks, grid, bpl);
+        return launch_small(st, spec, tile_blocks, grid, bpl, true);
     int rc;
     BatchCtx *c = get_ctx(device, st, &rc);
     if (!c)
@@ -550,6 +553,9 @@ extern "C" int aes_ctr_crypt_batch_cfg(const aes_ctr_desc_t *desc, size_t n, con
         if (cfg->blocks_per_lane) sh.bpl = cfg->blocks_per_lane;
         sh.use_graph = cfg->use_graph;
     }
+    // Several lanes per block, whose workgroups have tiles of their own, only for
+    // callers who leave the tiles to the library.
+    const bool several = !cfg || (cfg->tile_bytes == 0 && cfg->blocks_per_lane == 0);
     DeviceInfo di;
     int rc = device_info(&di);
     if (rc != AES_OK)
@@ -583,7 +589,7 @@ extern "C" int aes_ctr_crypt_batch_cfg(const aes_ctr_desc_t *desc, size_t n, con
         spec.n = n;
         spec.keys = keys;
         spec.n_keys = n;
-        return launch_small(st, spec, tile_blocks, sh.grid, sh.bpl);
+        return launch_small(st, spec, tile_blocks, sh.grid, sh.bpl, several);
     }
 
     // Otherwise launches of up to kMaxBatch requests, each request's key
@@ -609,7 +615,7 @@ extern "C" int aes_ctr_crypt_batch_cfg(const aes_ctr_desc_t *desc, size_t n, con
                 out[i].key = static_cast<uint32_t>(i);
             }
         });
-        const bool quad = sh.use_graph == 0 && quad_table(out, m, sh.grid);
+        const bool quad = several && !(cfg && cfg->wg_size) && sh.use_graph == 0 && quad_table(out, m, sh.grid);
         const size_t bytes = finish_stage(buf, m, quad ? kQuadTileBlocks : tile_blocks, sh.grid, quad);
         if (bytes == 0)
             return AES_ERANGE;

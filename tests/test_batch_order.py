@@ -46,3 +46,16 @@ def test_a_start_counter_adds_no_round_of_tiles(exe, n, size, tile):
     even, odd = routes(exe, [(n, size, 0, tile, 0, 0, 0), (n, size, 1, tile, 0, 0, 0)])
     assert even[0] == "small" and even[1] % 2048 == 0, even
     assert odd[0] == "small_plain" and odd[1:3] == even[1:3], odd
+
+
+def test_explicit_tiles_are_the_tiles_of_the_launch(exe):
+    """(requests, bytes): small enough to run with several lanes per block where the tiles are left to the library."""
+    for n, size, kernel in ((1, 4096, "quad"), (8, 65536, "quad"), (1, 1 << 20, "pair"), (9, 1000, "quad_table"),
+                            (200, 1500, "quad_table")):
+        assert routes(exe, [(n, size, 1, 0, 0, 0, 0)])[0][0] == kernel
+        for tile, bpl in ((1024, 0), (65536, 0), (0, 1), (0, 2), (4096, 1)):
+            got = routes(exe, [(n, size, 0, tile, bpl, 0, 0)])[0]
+            assert got[0] == ("table" if n > 8 else "small"), (n, size, tile, bpl, got)
+            assert got[4] == (bpl or 2), got
+            if tile:
+                assert got[1:3] == (n * -(-size // tile), tile // 16), (n, size, tile, got)
