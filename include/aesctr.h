@@ -222,7 +222,8 @@ int aes_ctr_crypt_batch(const aes_ctr_desc_t *desc, size_t n, void *stream);
  * Where tile_bytes and blocks_per_lane (and, for more than 8 requests, wg_size and
  * use_graph) are zero, up to 256 requests may run with four lanes per block, in
  * 256-thread workgroups of 64 blocks, up to twice `grid` of them, and up to 8
- * requests with two, in 512-thread workgroups of 256 blocks, up to `grid`. */
+ * requests with two, in 512-thread workgroups of 256 blocks, up to `grid` (a grid
+ * above the CU count counts as that). */
 typedef struct {
     int32_t tile_bytes;
     int32_t wg_size;

@@ -220,7 +220,7 @@ namespace {
 constexpr size_t kRecordGrain = 256;
 
 // Whether the requests in a staged table run with four lanes per block
-// (ctr_quad_table_kernel): at most two of its workgroups per CU of the grid, the
+// (ctr_quad_table_kernel): at most two of its workgroups for each of `cus`, the
 // small batch's limit, and no more requests than its waves look through.  us per
 // call back to back, and for one call up to its end, in brackets as tiles of the
 // table kernel: 9 requests of 0.1-1 KB 10.4 (15.0) and 18.2 (22.4), 64 of them 11.1
@@ -228,14 +228,14 @@ constexpr size_t kRecordGrain = 256;
 // KB 11.2 (15.3) and 19.4 (23.0).  Not through a captured graph, whose second node
 // is the table kernel, nor where the caller names that kernel's tiles, blocks per
 // lane or workgroup size.
-bool quad_table(const BatchDesc *descs, size_t n, int grid)
+bool quad_table(const BatchDesc *descs, size_t n, int cus)
 {
     if (n > kQuadTableReqs)
         return false;
     uint64_t tiles = 0;
     for (size_t i = 0; i < n; ++i)
         tiles += plain_tiles(descs[i].len, kQuadTileBlocks);
-    return tiles <= 2 * static_cast<uint64_t>(grid);
+    return tiles <= 2 * static_cast<uint64_t>(cus);
 }
 
 // How the tiles of a small batch are cut for `waves` waves (run_tile): by position,
@@ -257,12 +257,14 @@ bool shifted_tiles(uint64_t plain, uint64_t shifted, uint64_t waves, uint32_t ti
 
 // A batch of at most kSmallBatch requests goes in the kernel's argument block
 // (no staging slot, no upload), to one of three kernels whose grid it sizes.
-// Where four lanes per block make at most two workgroups per CU of the table
-// kernel's grid (which is at most one per CU), the requests run so
-// (ctr_quad.hip); else with two lanes per block where that makes at most one
-// (ctr_pair.hip); the limits are the single message's (quad_shape, pair_shape).
-// Else a wave per tile in workgroups of four waves, at most two workgroups per CU
-// too, the waves looping over further tiles.  us per call back to back, and for
+// Where four lanes per block make at most two workgroups for each of `cus`, the
+// requests run so (ctr_quad.hip); else with two lanes per block where that makes at
+// most one (ctr_pair.hip); the limits are the single message's (quad_shape,
+// pair_shape), and cus the smaller of the grid and the chip's CUs: beyond two
+// workgroups per CU a wave per tile is faster (4 requests of 1 MiB 9.3 us against
+// 11.7 as quads, of 4 MiB 23.8 against 36.6), which a larger grid does not change.
+// Else a wave per tile in workgroups of four waves, at most two workgroups per
+// workgroup of `grid`, the waves looping over further tiles.  us per call back to back, and for
 // one call up to its end, in brackets those of the last kernel.  Quads: one
 // request of 64 KiB 4.6 (7.8) and 15.2 (19.5); one of 512 KiB 4.6 (8.0) and 16.0
 // (19.6); 8 of 100 bytes 4.8 (8.7) and 15.2 (19.3); 8 of 64 KiB 4.8 (9.6) and 16.0
@@ -271,10 +273,10 @@ bool shifted_tiles(uint64_t plain, uint64_t shifted, uint64_t waves, uint32_t ti
 // host memory 47.5 (49.7).
 // several: whether the first two may take it (not where the caller names the last
 // one's tiles or blocks per lane).  Returns AES_OK, AES_ERANGE or AES_EDEVICE.
-int launch_small(hipStream_t st, const LaunchSpec &spec, uint32_t tile_blocks, int grid, int bpl, bool several)
+int launch_small(hipStream_t st, const LaunchSpec &spec, uint32_t tile_blocks, int grid, int cus, int bpl, bool several)
 {
     SmallBatchArgs args{};
-    const uint64_t cap = 2 * static_cast<uint64_t>(grid);
+    const uint64_t cap = 2 * static_cast<uint64_t>(grid), pair_cap = static_cast<uint64_t>(cus), quad_cap = 2 * pair_cap;
     uint64_t quads = 0, pairs = 0, plain = 0, shifted = 0;
     for (size_t i = 0; i < spec.n; ++i) {
         const BatchDesc &d = spec.descs[i];
@@ -283,11 +285,11 @@ int launch_small(hipStream_t st, const LaunchSpec &spec, uint32_t tile_blocks, i
         plain += plain_tiles(d.len, tile_blocks);
         shifted += request_tiles(d.len, d.ctr0, tile_blocks);
     }
-    const bool quad = several && quads <= cap;
-    const bool pair = several && !quad && pairs <= static_cast<uint64_t>(grid);
+    const bool quad = several && quads <= quad_cap;
+    const bool pair = several && !quad && pairs <= pair_cap;
     if (quad || pair)
         tile_blocks = quad ? kQuadTileBlocks : kPairTileBlocks;
-    const bool shift = !quad && !pair && shifted_tiles(plain, shifted, 4 * cap, tile_blocks);
+    const bool shift = !quad && !pair && shifted_tiles(plain, shifted, 4 * quad_cap, tile_blocks);
     uint64_t tiles = 0;
     for (size_t i = 0; i < spec.n; ++i) {
         const BatchDesc &d = spec.descs[i];
@@ -389,7 +391,7 @@ int launch_spec(int device, hipStream_t st, const LaunchSpec &spec, int tile_byt
         spec.n_install > static_cast<size_t>(kMaxBatch))
         return AES_EINVAL;
     if (allow_small && spec.n <= kSmallBatch)
-        return launch_small(st, spec, tile_blocks, grid, bpl, true);
+        return launch_small(st, spec, tile_blocks, grid, grid, bpl, true);
     int rc;
     BatchCtx *c = get_ctx(device, st, &rc);
     if (!c)
@@ -562,6 +564,7 @@ extern "C" int aes_ctr_crypt_batch_cfg(const aes_ctr_desc_t *desc, size_t n, con
         return rc;
     if (sh.grid == 0)
         sh.grid = di.num_cus;
+    const int cus = std::min(sh.grid, di.num_cus);
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
@@ -589,7 +592,7 @@ extern "C" int aes_ctr_crypt_batch_cfg(const aes_ctr_desc_t *desc, size_t n, con
         spec.n = n;
         spec.keys = keys;
         spec.n_keys = n;
-        return launch_small(st, spec, tile_blocks, sh.grid, sh.bpl, several);
+        return launch_small(st, spec, tile_blocks, sh.grid, cus, sh.bpl, several);
     }
 
     // Otherwise launches of up to kMaxBatch requests, each request's key
@@ -615,7 +618,7 @@ extern "C" int aes_ctr_crypt_batch_cfg(const aes_ctr_desc_t *desc, size_t n, con
                 out[i].key = static_cast<uint32_t>(i);
             }
         });
-        const bool quad = several && !(cfg && cfg->wg_size) && sh.use_graph == 0 && quad_table(out, m, sh.grid);
+        const bool quad = several && !(cfg && cfg->wg_size) && sh.use_graph == 0 && quad_table(out, m, cus);
         const size_t bytes = finish_stage(buf, m, quad ? kQuadTileBlocks : tile_blocks, sh.grid, quad);
         if (bytes == 0)
             return AES_ERANGE;

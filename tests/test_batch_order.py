@@ -59,3 +59,13 @@ def test_explicit_tiles_are_the_tiles_of_the_launch(exe):
             assert got[4] == (bpl or 2), got
             if tile:
                 assert got[1:3] == (n * -(-size // tile), tile // 16), (n, size, tile, got)
+
+
+def test_several_lanes_per_block_stop_at_the_chips_size(exe):
+    """Quads up to two workgroups of 64 blocks per CU, pairs up to one of 256, however large the grid (256 CUs)."""
+    for grid in (0, 256, 257, 4096):
+        for n, size, kernel in ((8, 65536, "quad"), (4, 128 * 1024 + 1, "pair"), (4, 256 * 1024, "pair"), (4, 256 * 1024 + 1, "small"),
+                                (4, 1 << 20, "small"), (16, 32768, "quad_table"), (16, 32769, "table")):
+            assert routes(exe, [(n, size, 0, 0, 0, grid, 0)])[0][0] == kernel, (grid, n, size)
+    for n, size, kernel in ((8, 128, "quad"), (1, 2049, "pair"), (1, 4097, "small"), (9, 200, "table")):
+        assert routes(exe, [(n, size, 0, 0, 0, 1 if n == 1 else 4, 0)])[0][0] == kernel, (n, size)
