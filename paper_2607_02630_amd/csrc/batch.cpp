@@ -239,19 +239,25 @@ bool quad_table(const BatchDesc *descs, size_t n, int cus)
 }
 
 // How the tiles of a small batch are cut for `waves` waves (run_tile): by position,
-// where a request starts at ctr0 mod 64 and may need one tile more, or from its
-// start, where every step takes 3 to 8% longer.  The tiles more matter when they
-// make one more round of all waves.  us per call, by position and from the start,
-// requests from counter 1: one of 4 MiB (2049 or 2048 tiles, 2048 waves) 9.5 and
-// 7.7, four of 1 MiB 11.4 and 9.3, eight of 8 MiB (two rounds) 74.0 and 67.9.  Not
-// so among thirteen rounds, four where tiles have over 256 blocks (eight requests
-// of 32 MiB 246 and 259), nor for one or two such tiles, which a workgroup's oldest
-// wave takes while the others still work (one of 32 MiB 26.8 and 28.7, two of 16
-// MiB 31.9 and 33.8).
-bool shifted_tiles(uint64_t plain, uint64_t shifted, uint64_t waves, uint32_t tile_blocks)
+// where a request whose first counter is ctr0 mod 64 != 0 (`odd`: one is) lies across
+// the memory's lines and may need one step or tile more, or from its start, where
+// every step takes 3 to 8% longer.
+//  * One round of all waves takes as long as its longest tile, so an odd batch goes
+//    from the start: 4 requests of 8 KiB in one tile each from counter 1 19.8 us by
+//    position and 18.1 from the start, 4 of 300,000 bytes 8.7 and 8.5.
+//  * More rounds: from the start where the further tiles make one more: one request
+//    of 4 MiB from counter 1 (2049 or 2048 tiles, 2048 waves) 9.5 and 7.7, four of 1
+//    MiB 11.4 and 9.3, eight of 8 MiB (two rounds) 74.0 and 67.9.  Not so among
+//    thirteen rounds, four where tiles have over 256 blocks (eight requests of 32 MiB
+//    246 and 259), nor for one or two such tiles, which a workgroup's oldest wave takes
+//    while the others still work (one of 32 MiB 26.8 and 28.7, two of 16 MiB 31.9 and
+//    33.8).
+bool by_position(uint64_t plain, uint64_t shifted, bool odd, uint64_t waves, uint32_t tile_blocks)
 {
     const uint64_t rounds = (plain + waves - 1) / waves;
     const bool large = tile_blocks > 256;
+    if (rounds <= 1)
+        return !odd;
     return (shifted + waves - 1) / waves == rounds || rounds >= (large ? 4 : 13) || (large && shifted - plain <= 2);
 }
 
@@ -278,18 +284,20 @@ int launch_small(hipStream_t st, const LaunchSpec &spec, uint32_t tile_blocks, i
     SmallBatchArgs args{};
     const uint64_t cap = 2 * static_cast<uint64_t>(grid), pair_cap = static_cast<uint64_t>(cus), quad_cap = 2 * pair_cap;
     uint64_t quads = 0, pairs = 0, plain = 0, shifted = 0;
+    bool odd = false;
     for (size_t i = 0; i < spec.n; ++i) {
         const BatchDesc &d = spec.descs[i];
         quads += plain_tiles(d.len, kQuadTileBlocks);
         pairs += plain_tiles(d.len, kPairTileBlocks);
         plain += plain_tiles(d.len, tile_blocks);
         shifted += request_tiles(d.len, d.ctr0, tile_blocks);
+        odd = odd || (d.len != 0 && (d.ctr0 & 63u) != 0);
     }
     const bool quad = several && quads <= quad_cap;
     const bool pair = several && !quad && pairs <= pair_cap;
     if (quad || pair)
         tile_blocks = quad ? kQuadTileBlocks : kPairTileBlocks;
-    const bool shift = !quad && !pair && shifted_tiles(plain, shifted, 4 * quad_cap, tile_blocks);
+    const bool shift = !quad && !pair && by_position(plain, shifted, odd, 4 * quad_cap, tile_blocks);
     uint64_t tiles = 0;
     for (size_t i = 0; i < spec.n; ++i) {
         const BatchDesc &d = spec.descs[i];

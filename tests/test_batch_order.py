@@ -48,6 +48,14 @@ def test_a_start_counter_adds_no_round_of_tiles(exe, n, size, tile):
     assert odd[0] == "small_plain" and odd[1:3] == even[1:3], odd
 
 
+@pytest.mark.parametrize("n,size,tile,bpl", [(2, 1 << 20, 0, 0), (4, 300_000, 0, 0), (4, 8192, 65536, 2), (3, 3072, 4096, 1),
+                                             (1, 2 << 20, 0, 0)])
+def test_a_start_counter_adds_no_step_to_one_round(exe, n, size, tile, bpl):
+    even, odd = routes(exe, [(n, size, 64, tile, bpl, 0, 0), (n, size, 127, tile, bpl, 0, 0)])
+    assert even[0] == "small" and even[1] <= 2048, even
+    assert odd[0] == "small_plain" and odd[1:] == even[1:], odd
+
+
 def test_explicit_tiles_are_the_tiles_of_the_launch(exe):
     """(requests, bytes): small enough to run with several lanes per block where the tiles are left to the library."""
     for n, size, kernel in ((1, 4096, "quad"), (8, 65536, "quad"), (1, 1 << 20, "pair"), (9, 1000, "quad_table"),
