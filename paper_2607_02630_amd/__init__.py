@@ -257,10 +257,12 @@ def aes_ctr_crypt_batch_noalloc(reqs, stream=None, descs=None) -> None:
 
 
 def batch_cfg(tile_bytes: int = 0, wg_size: int = 0, grid: int = 0, blocks_per_lane: int = 0,
-              use_graph: int = 1) -> aes_batch_cfg_t:
+              use_graph: int = 0) -> aes_batch_cfg_t:
     """Launch shape for aes_ctr_crypt_batch (aes_batch_cfg_t); zero fields keep
-    the default (tiles sized to the batch, one 1024-thread workgroup per CU,
-    two blocks per lane, the captured graph)."""
+    the default: tiles sized to the batch, one 1024-thread workgroup per CU,
+    two blocks per lane, two plain launches (use_graph = 1: a captured graph of
+    them, slower at every size), and several lanes per block for few small
+    requests.  batch_cfg() is the call without a cfg."""
     c = aes_batch_cfg_t()
     c.tile_bytes, c.wg_size, c.grid, c.blocks_per_lane, c.use_graph = (
         tile_bytes, wg_size, grid, blocks_per_lane, use_graph)

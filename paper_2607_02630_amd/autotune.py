@@ -12,7 +12,8 @@ candidate replaces it only when at least 1% faster.  The chosen shape per
 (AESCTR_TUNE_CACHE or tune_cache.json next to the library).
 
 The batch kernel's tile sizing (tiles per CU, largest tile) and blocks per
-lane are tuned on the 4096-request batch workload, encrypting zero payloads
+lane are tuned on the 4096-request batch workload, launched as a call without a
+cfg launches it (two plain launches), encrypting zero payloads
 so that the output is the keystream: each candidate's sampled keystream
 blocks must hash to the digest in --golden.
 
@@ -239,7 +240,7 @@ def tune_batch(torch, A, W, cus, expect: str):
     # largest tile and the blocks per lane are searched, the rule's own
     # (64 KiB, 2) first.
     tpc = 16
-    for _ in range(3):          # warm-up: staging, graphs and clocks
+    for _ in range(3):          # warm-up: staging and clocks
         A.aes_ctr_crypt_batch(objs, cfg=A.batch_cfg(tile_bytes=65536, blocks_per_lane=2), descs=arr)
     torch.cuda.synchronize()
     for max_tile, bpl in [(65536, 2)] + list(itertools.product((16384, 32768, 65536, 131072, 262144), (1, 2))):

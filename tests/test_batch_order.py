@@ -77,3 +77,13 @@ def test_several_lanes_per_block_stop_at_the_chips_size(exe):
             assert routes(exe, [(n, size, 0, 0, 0, grid, 0)])[0][0] == kernel, (grid, n, size)
     for n, size, kernel in ((8, 128, "quad"), (1, 2049, "pair"), (1, 4097, "small"), (9, 200, "table")):
         assert routes(exe, [(n, size, 0, 0, 0, 1 if n == 1 else 4, 0)])[0][0] == kernel, (n, size)
+
+
+def test_an_empty_configuration_is_the_default_call(exe):
+    """The binding's batch_cfg() names nothing, the graph included, so few small requests keep their kernel."""
+    import paper_2607_02630_amd as A
+    cfg = A.batch_cfg()
+    fields = (cfg.tile_bytes, cfg.blocks_per_lane, cfg.grid, cfg.use_graph)
+    assert fields == (0, 0, 0, 0) and cfg.wg_size == 0
+    assert routes(exe, [(64, 1000, 1, *fields)])[0][0] == "quad_table"
+    assert A.batch_cfg(grid=3).use_graph == 0 and A.batch_cfg(use_graph=1).use_graph == 1
