@@ -12,7 +12,7 @@
 // v_alignbit_b32, Ch / Maj / three-way XORs single v_bitop3_b32, and the sums
 // v_add3_u32.  The host orders a launch's messages longest first, so lanes of
 // a wave run for similar lengths.  Bound by VALU issue: 1402 instructions per
-// block, 512 MiB in 4 KiB messages in 364 us = 1475 GB/s of the 1795 that
+// block, 512 MiB in 4 KiB messages in 369 us = 1455 GB/s of the 1795 that
 // 64 lanes per clock at 2.4 GHz would give.  Few messages: bound by one
 // message's chain of blocks, see sha256_split_kernel.
 #include <hip/hip_runtime.h>
@@ -167,12 +167,15 @@ typedef const __attribute__((address_space(1))) uint8_t g_cu8;
 
 __device__ __forceinline__ g_cu8 *msg_ptr(uint64_t in) { return reinterpret_cast<g_cu8 *>(static_cast<uintptr_t>(in)); }
 
-// The sixteen words of a full block at p, as they lie in memory.
+// The sixteen words of a full block at p, as they lie in memory.  Ordinary loads: a
+// lane comes back to a 128-byte line for the next block, and off alignment for a
+// third one, which a non-temporal hint has read from memory again (131,072 messages
+// of 4 KiB 408 us a call instead of 374, one byte off alignment 442 instead of 386).
 __device__ __forceinline__ void load_raw(g_cu8 *p, u32x4 d[4])
 {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-        d[i] = __builtin_nontemporal_load(reinterpret_cast<g_cu32x4 *>(p) + i);
+        d[i] = reinterpret_cast<g_cu32x4 *>(p)[i];
 }
 
 __device__ __forceinline__ void to_words(const u32x4 d[4], uint32_t w[16])
@@ -229,9 +232,9 @@ __device__ __forceinline__ void store_words(uint64_t to, const uint32_t H[4])
 // One lane per message.  The next block's loads, and the tail's, are in
 // flight while a block compresses; the one or two padding blocks run in a
 // loop of their own, so a wave pays for them once whatever its lanes' lengths.
-// Messages at any address take the same 16-byte loads (64 byte loads per
-// block before: 65,536 unaligned messages of 4 KiB 230 -> 224 us, aligned ones
-// 220 -> 206).
+// Messages at any address take the same 16-byte loads (64 byte loads per block
+// before: 65,536 messages of 4 KiB one byte off alignment 238 -> 206 us a call, aligned
+// ones 228 -> 194).
 __global__ __launch_bounds__(256) void sha256_batch_kernel(const ShaRecord *__restrict__ recs, uint32_t n)
 {
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {

@@ -177,7 +177,11 @@ int stage_and_launch(int device, hipStream_t st, size_t n, int num_cus, Fill fil
         // Up to two of the split kernel's workgroups (64 messages, three
         // waves) per CU its shorter chain wins: 4 KiB messages, per call,
         // 16,384 of them 111 against 193 us, 32,768 181 against 197, 49,152
-        // 239 against 201 (by then one lane per message fills the SIMDs).
+        // 239 against 201 (by then one lane per message fills the SIMDs).  Also
+        // for messages of a block or two, whose calls are mostly the host's and
+        // the records' way over PCIe: us per call back to back, 64 messages of
+        // 100 bytes 27.9 (33.2), 4096 37.0 (41.5), 16,384 37.2 (40.5), 32,768 57.1
+        // (65.4); 32,768 of 0 bytes 50.9 (53.2), of 256 63.1 (65.4).
         const bool split = groups <= static_cast<uint32_t>(num_cus) / 2;
         const ShaRecord *recs = c->host_view[slot];
         if (first > 0 || hipStreamQuery(st) != hipSuccess) {
