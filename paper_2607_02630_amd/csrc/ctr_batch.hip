@@ -12,9 +12,10 @@
 // AES-256 mixed) and alignment share the launch; dynamic claiming balances
 // the log-uniform size mix.
 //
-// Bound: 4.5 GB in 4096 requests takes 3.0 ms at 128 (AES-128) or 192 table
-// lookups per block, 27 of the 28.6 per clock and CU that the LDS gives, at the
-// 2.0-2.1 GHz the card holds under this load (2.4 without the payload traffic).
+// Bound: 4.5 GB in 4096 requests takes 3.0-3.2 ms at 129.7 (AES-128) or 193.8 table
+// lookups per block, counted: 30 of the 32 per clock and CU that the LDS's two clocks
+// per instruction allow, at the 1.9-2.0 GHz the card holds under this load (2.4
+// without the payload traffic).
 #include <stddef.h>
 
 #include "ttable_tile.h"

@@ -11,9 +11,10 @@
 // the issue slot, so with equal shares the first waves of a workgroup end at 95
 // of 155 us and the last work alone.
 //
-// Bound: 128 (AES-256: 192) table lookups and 201 (297) VALU instructions per
-// block; the LDS gives 27 of its 28.6 lookups per clock and CU, at the 2.0-2.1
-// GHz the card holds under this load (2.4 without the payload traffic).
+// Bound: 129.6 (AES-256: 193.6) table lookups and 215 (313) VALU instructions per
+// block, counted; the LDS gives 26.5 (27.9) of the 32 lookups per clock and CU that
+// its two clocks per instruction allow, at the 2.0-2.1 GHz the card holds under this
+// load (2.4 without the payload traffic).
 // Measured: 256 MiB AES-128 153 us = 1755 GB/s (167 before, two 512-thread
 // workgroups with equal shares per CU), AES-256 208 us = 1290 GB/s (230); ragged
 // 100 MB AES-256 in place 80 us (89).

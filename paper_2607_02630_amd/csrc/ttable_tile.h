@@ -19,8 +19,8 @@ namespace {
 // counters (group_consts_lds for 64 consecutive groups at a time, a lane each,
 // handed over with v_readlane): four XORs per block where the wave's scalar
 // constants took 5 lookups, 15 VALU instructions and a chain of scalar loads
-// per step (main loop of the four-table kernel, AES-128: 128 lookups and 202
-// VALU instructions per block, 133 and 238 before).
+// per step (main loop of the four-table kernel by its listing, AES-128: 128 lookups
+// and 202 VALU instructions per block, 133 and 238 before).
 __host__ __device__ __forceinline__ uint32_t message_shift(uint32_t ctr0) { return ctr0 & 63u; }
 
 // Round 2 of every column without its group constant, for counters whose low
