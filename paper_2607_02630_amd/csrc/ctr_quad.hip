@@ -147,6 +147,25 @@ __global__ __launch_bounds__(kQuadWG) void ctr_quad_kernel(const uint8_t *in, ui
     quad_store(out, at, len, whole, d);
 }
 
+// A lane's word d of a request of either key size, whose key material from word c on
+// is ks (quad_keys), from behind its load to its store.
+__device__ __forceinline__ void quad_crypt(const uint32_t *lds, const uint32_t *ks, uint32_t c, const uint8_t *in,
+                                           uint8_t *out, uint64_t at, uint64_t len, bool whole, uint32_t d,
+                                           uint32_t ctr, uint32_t x0, uint32_t nr)
+{
+    d = quad_load_rest(in, at, len, whole, d);
+    if (nr == 10) {
+        uint32_t k[11];
+        quad_keys<10>(ks, k);
+        d ^= quad_keystream<10>(lds, k, c, ctr, x0);
+    } else {
+        uint32_t k[15];
+        quad_keys<14>(ks, k);
+        d ^= quad_keystream<14>(lds, k, c, ctr, x0);
+    }
+    quad_store(out, at, len, whole, d);
+}
+
 // A few small requests whose records travel in the kernel argument block
 // (SmallBatchArgs, tile_blocks = kBlocks): workgroup t takes tile t.
 __global__ __launch_bounds__(kQuadWG) void ctr_quad_batch_kernel(const SmallBatchArgs args)
@@ -183,20 +202,8 @@ __global__ __launch_bounds__(kQuadWG) void ctr_quad_batch_kernel(const SmallBatc
     lkeys[threadIdx.x] = kw;
     uint32_t d = quad_load(in, at, len, whole);
     __syncthreads();
-    if (any) {
-        d = quad_load_rest(in, at, len, whole, d);
-        const uint32_t *ks = lkeys + 64 * wave + c;
-        if (nr == 10) {
-            uint32_t k[11];
-            quad_keys<10>(ks, k);
-            d ^= quad_keystream<10>(lds, k, c, ctr, x0);
-        } else {
-            uint32_t k[15];
-            quad_keys<14>(ks, k);
-            d ^= quad_keystream<14>(lds, k, c, ctr, x0);
-        }
-        quad_store(out, at, len, whole, d);
-    }
+    if (any)
+        quad_crypt(lds, lkeys + 64 * wave + c, c, in, out, at, len, whole, d, ctr, x0, nr);
     // No wave of this launch reads a slot that it installs.
     if (t == 0) {
         for (uint32_t j = threadIdx.x; j < 64u * n; j += kQuadWG) {
@@ -249,20 +256,8 @@ __global__ __launch_bounds__(kQuadWG) void ctr_quad_table_kernel(const uint8_t *
     lkeys[threadIdx.x] = kw;
     uint32_t d = quad_load(in, at, len, whole);
     __syncthreads();
-    if (any) {
-        d = quad_load_rest(in, at, len, whole, d);
-        const uint32_t *ks = lkeys + 64 * wave + c;
-        if (nr == 10) {
-            uint32_t k[11];
-            quad_keys<10>(ks, k);
-            d ^= quad_keystream<10>(lds, k, c, ctr, x0);
-        } else {
-            uint32_t k[15];
-            quad_keys<14>(ks, k);
-            d ^= quad_keystream<14>(lds, k, c, ctr, x0);
-        }
-        quad_store(out, at, len, whole, d);
-    }
+    if (any)
+        quad_crypt(lds, lkeys + 64 * wave + c, c, in, out, at, len, whole, d, ctr, x0, nr);
     // No wave of this launch reads a slot that it installs.
     if (t == 0) {
         const InstallRec *inst = reinterpret_cast<const InstallRec *>(table + install_off);
